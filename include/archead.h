@@ -186,7 +186,8 @@ void archead_destroy(archead_handle* h);
 /* Bytes of workspace the call `op` needs for M tokens (0 for M == 0).  The
  * workspace holds the low-rank projections t (fp32 [M, r_c + r_r]; on the
  * decode and several-token paths with a 32-bit call stamp beside each value; on the tiled
- * MFMA path split into three bf16 parts), on the tiled path also per-call
+ * MFMA path split into three bf16 parts), on the tiled path also a copy of x
+ * (2 * M * d bytes, each token scaled by a power of two) and per-call
  * tables derived from the head (group-scale ratios, the per-group sums of x,
  * the factor codes as bf16 and the U_c / A_w codes side by side: about
  * V * (r_c + r_r + 4 * (d/g + 3)) bytes, used only while the head has no
@@ -332,20 +333,22 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
                                    int64_t ldx, int32_t k, float* vals, int64_t* idx,
                                    int64_t ldk, void* ws, size_t ws_bytes, void* stream);
 
-/* Bytes of the static workspace of archead_logits_noalloc, one array per
- * device the library runs on (kept until the process ends). */
+/* Limit of the workspace archead_logits_noalloc counts for a call; its static
+ * array, one per device the library runs on (kept until the process ends),
+ * holds 4 MiB more for the parts not counted. */
 #define ARCHEAD_NOALLOC_SCRATCH_BYTES (4u << 20)
 
 /* archead_logits without a caller workspace, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation.  Same arguments, results and
  * kernels as archead_logits (bit-identical logits), except that the
- * workspace is a static device array of ARCHEAD_NOALLOC_SCRATCH_BYTES bytes
- * inside the library, whose device address archead_create takes once per
+ * workspace is a static device array inside the library, whose device address archead_create takes once per
  * device.  The call allocates nothing (no hipMalloc, no allocating library
  * routine).
- *   Limit: M whose archead_workspace_bytes(h, M, ARCHEAD_OP_LOGITS) exceeds
- *   ARCHEAD_NOALLOC_SCRATCH_BYTES is rejected with ARCHEAD_E_WORKSPACE (the
+ *   Limit: M whose archead_workspace_bytes(h, M, ARCHEAD_OP_LOGITS), without
+ *   the many-token path's copy of x and group sums, exceeds
+ *   ARCHEAD_NOALLOC_SCRATCH_BYTES is rejected with ARCHEAD_E_WORKSPACE; where
+ *   those do not fit beside the rest, the call runs in chunks of tokens (the
  *   decode-shaped paths fit: at the Qwen3-8B shape, r_c + r_r = 96, every M
  *   up to 32; the many-token path's per-call tables do not).
  *   All calls on one GPU share that GPU's array, which keeps the last call's

@@ -291,7 +291,7 @@ PrepLayout prep_layout(const archead_handle* h) {
   p.wbf_off = off;
   off = align256(off + sizeof(uint16_t) * size_t(d.r_c + d.r_r) * size_t(d.d));
   p.uc_off = off;
-  off = align256(off + size_t(d.V) * nch * 32);                    // [c|c] x 16
+  off = align256(off + size_t(d.V) * nch * 32);   // [c|c] x 16
   p.total = off;
   return p;
 }
@@ -369,14 +369,15 @@ WsLayout ws_layout(const archead_handle* h, int64_t M, archead_op op) {
     const size_t n_vt = size_t((h->desc.V + kTN - 1) / kTN);
     w.fid_off = w.total;
     w.bref_off = align256(w.fid_off + 32 * size_t(M) * n_vt);
-    w.total = align256(w.bref_off + sizeof(float) * size_t(M));
+    w.need_off = align256(w.bref_off + sizeof(float) * size_t(M));
+    w.total = align256(w.need_off + sizeof(int) * ((size_t(M) + 63) / 64) * n_vt);
     return w;
   }
   return ws_layout_path(h, M, op, h ? choose_path(h, M) : Path::kGemv);
 }
 
-// The layout for M tokens on the kernel `path`.
-WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path path) {
+// The layout for M tokens on the kernel `path` (tokens of a call of call_M).
+WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path path, int64_t call_M) {
   WsLayout w;
   if (!h || M <= 0) return w;
   const archead_desc& d = h->desc;
@@ -390,24 +391,27 @@ WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path 
     off = align256(off + sizeof(uint64_t) * size_t(M) * size_t(d.r_c + d.r_r));
   } else {
     const size_t ngrp = size_t(d.d / d.g);
-    const size_t nslot = ngrp + (d.r_c ? 1 : 0) + (d.r_r ? 1 : 0);
     const size_t nch = size_t(exp_chunks(d.r_c) + exp_chunks(d.r_r));
     const size_t n_mt = size_t((M + kTM - 1) / kTM);
     w.ts_off = off;
     off = align256(off + sizeof(uint16_t) * size_t(M) * nch * 64);   // [hi|mid|lo|0] x 16
+    w.xs_off = off;
+    off = align256(off + sizeof(uint16_t) * size_t(M) * size_t(d.d));
+    w.re_off = off;
+    off = align256(off + sizeof(float) * n_mt * kTM);
+    w.gs_off = off;
+    off = align256(off + sizeof(float) * size_t(M) * ngrp);
     w.gb_off = off;
-    off = align256(off + sizeof(float) * n_mt * nslot * kTM);
+    off = align256(off + sizeof(float) * n_mt * ngrp * kTM);
     const PrepLayout pl = prep_layout(h);
     w.rat_off = off + pl.rat_off;
     w.fin_off = off + pl.fin_off;
     w.wbf_off = off + pl.wbf_off;
     w.uc_off = off + pl.uc_off;
     off += pl.total;
-    const int ks = s1_ksplit(h, M);
-    if (ks > 1) {
-      w.s1p_off = off;
-      off = align256(off + sizeof(float) * size_t(ks) * size_t(M) * size_t(d.r_c + d.r_r));
-    }
+    w.ksplit = s1_ksplit(h, call_M ? call_M : M);
+    w.s1p_off = off;
+    off = align256(off + sizeof(float) * size_t(w.ksplit) * size_t(M) * size_t(d.r_c + d.r_r));
   }
   if (op == ARCHEAD_OP_LOGITS_CE || op == ARCHEAD_OP_ARGMAX) {
     // GEMV: all CE passes share one grid (the smallest of the variants
@@ -445,8 +449,7 @@ using namespace archead;
 
 namespace {
 
-archead_status check_call(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
-                          const void* ws, size_t ws_bytes, archead_op op) {
+archead_status check_args(const archead_handle* h, const void* x, int64_t M, int64_t ldx) {
   if (!h) return fail(ARCHEAD_E_INVALID_ARG, "handle is NULL");
   if (M < 0) return fail(ARCHEAD_E_INVALID_ARG, "M = %lld < 0", (long long)M);
   if (M == 0) return ARCHEAD_OK;
@@ -454,10 +457,27 @@ archead_status check_call(const archead_handle* h, const void* x, int64_t M, int
   if (!x) return fail(ARCHEAD_E_INVALID_ARG, "x is NULL");
   if (ldx < h->desc.d) return fail(ARCHEAD_E_INVALID_ARG, "ldx < d");
   if (!aligned(x, 16) || ldx % 8) return fail(ARCHEAD_E_MISALIGNED, "x must be 16-byte aligned with ldx %% 8 == 0");
+  return ARCHEAD_OK;
+}
+
+archead_status check_call(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
+                          const void* ws, size_t ws_bytes, archead_op op) {
+  const archead_status st = check_args(h, x, M, ldx);
+  if (st != ARCHEAD_OK || M == 0) return st;
   const size_t need = ws_layout(h, M, op).total;
   if (ws_bytes < need) return fail(ARCHEAD_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   if (need && !ws) return fail(ARCHEAD_E_INVALID_ARG, "workspace is NULL");
   if (!aligned(ws, 256)) return fail(ARCHEAD_E_MISALIGNED, "workspace must be 256-byte aligned");
+  return ARCHEAD_OK;
+}
+
+archead_status check_out(const archead_handle* h, const void* out, archead_dtype out_dtype, int64_t ldo) {
+  if (!out) return fail(ARCHEAD_E_INVALID_ARG, "out is NULL");
+  if (out_dtype != ARCHEAD_F32 && out_dtype != ARCHEAD_BF16)
+    return fail(ARCHEAD_E_INVALID_ARG, "out_dtype must be ARCHEAD_F32 or ARCHEAD_BF16");
+  if (ldo < h->desc.V) return fail(ARCHEAD_E_INVALID_ARG, "ldo < V");
+  if (!aligned(out, out_dtype == ARCHEAD_F32 ? 4 : 2))
+    return fail(ARCHEAD_E_MISALIGNED, "out is not aligned to its element size");
   return ARCHEAD_OK;
 }
 
@@ -509,13 +529,16 @@ archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
 }
 
 // MFMA path prologue: the head-derived tables (unless the head has them
-// prepared), then stage 1 (t and the group biases).
+// prepared), then stage 1 (t, the slot biases and the scaled x; `even`: without
+// the odd code pairs' 1 / 16, for the passes that read a dense head too).
 archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int64_t M,
-                                    int64_t ldx, const WsLayout& w, char* ws, hipStream_t s) {
+                                    int64_t ldx, const WsLayout& w, char* ws, hipStream_t s,
+                                    bool even = false) {
   const archead_desc& d = h->desc;
   const int R = int(d.r_c + d.r_r);
-  const int nch_u = exp_chunks(d.r_c), nch = nch_u + exp_chunks(d.r_r);
-  const int nslot = int(d.d / d.g) + (d.r_c ? 1 : 0) + (d.r_r ? 1 : 0);
+  // 256 rows of x span less than 2 GiB
+  if (int64_t(kTM) * ldx * 2 >= (int64_t(1) << 31) && !even)
+    return fail(ARCHEAD_E_UNSUPPORTED, "ldx too large for the many-token kernel");
   char* pb = prep_base(h, w, ws);
   if (!h->prep.load(std::memory_order_acquire)) {
     archead_status st = launch_prep(h, pb, s);
@@ -530,23 +553,27 @@ archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int6
   a.sb = static_cast<const uint16_t*>(h->ptrs.corr_b_scale);
   a.gb = int(d.r_r ? d.g_b : d.d); a.rr = int(d.r_r);
   a.tsplit = reinterpret_cast<uint16_t*>(ws + w.ts_off);
-  a.nch = nch; a.nch_u = nch_u;
+  a.nch_u = exp_chunks(d.r_c);
+  a.nch = a.nch_u + exp_chunks(d.r_r);
   a.gbias = reinterpret_cast<float*>(ws + w.gb_off);
-  a.nslot = nslot;
-  a.ksplit = s1_ksplit(h, M);
+  a.gsum = reinterpret_cast<float*>(ws + w.gs_off);
+  a.xs = reinterpret_cast<uint16_t*>(ws + w.xs_off);
+  a.rowexp = reinterpret_cast<float*>(ws + w.re_off);
+  a.even = even;
+  a.ksplit = w.ksplit;
   a.tpart = reinterpret_cast<float*>(ws + w.s1p_off);
   const int64_t mblocks = (M + kS1MTok - 1) / kS1MTok;
   const int64_t rblocks = R > 0 ? (R + kS1MCols - 1) / kS1MCols : 1;
-  if (mblocks > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "M too large");
+  const int64_t grid = mblocks * rblocks * a.ksplit + M;
+  const int64_t mpad = (M + kTM - 1) / kTM * kTM;
+  const int64_t fgrid = (M * a.nch * kExpDims + mpad * (d.d / d.g) + kBlock - 1) / kBlock;
+  if (grid > 0x7fffffff || fgrid > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "M too large");
+  a.mblocks = int(mblocks);
+  a.rblocks = int(rblocks);
   void* args[] = {&a};
-  hipError_t e = hipLaunchKernel(kern::stage1m(),
-                                 dim3(unsigned(mblocks), unsigned(rblocks), unsigned(a.ksplit)),
-                                 dim3(kS1MBlock), args, 0, s);
-  if (e == hipSuccess && a.ksplit > 1) {
-    const int64_t n = M * R;
-    e = hipLaunchKernel(kern::stage1m_fin(), dim3(unsigned((n + kBlock - 1) / kBlock)),
-                        dim3(kBlock), args, 0, s);
-  }
+  hipError_t e = hipLaunchKernel(kern::stage1m(), dim3(unsigned(grid)), dim3(kS1MBlock), args, 0, s);
+  if (e == hipSuccess)
+    e = hipLaunchKernel(kern::stage1m_fin(), dim3(unsigned(fgrid)), dim3(kBlock), args, 0, s);
   return e == hipSuccess ? ARCHEAD_OK : hip_fail(e, "stage-1 launch");
 }
 
@@ -785,19 +812,19 @@ TiledShape tiled_shape(const archead_handle* h, int64_t M) {
   return t;
 }
 
-MfmaArgs mfma_args(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
-                   const WsLayout& w, char* ws) {
+MfmaArgs mfma_args(const archead_handle* h, int64_t M, const WsLayout& w, char* ws) {
   const archead_desc& d = h->desc;
   MfmaArgs a;
   memset(&a, 0, sizeof a);
   a.codes = static_cast<const uint8_t*>(h->ptrs.res_codes);
-  a.x = static_cast<const uint16_t*>(x);
-  a.ldx = ldx;
+  a.x = reinterpret_cast<const uint16_t*>(ws + w.xs_off);
+  a.ldx = d.d;
   a.tsplit = reinterpret_cast<const uint16_t*>(ws + w.ts_off);
   const PrepLayout pl = prep_layout(h);
   const char* pb = prep_base(h, w, ws);
   a.ucodes = reinterpret_cast<const int8_t*>(pb + pl.uc_off);
   a.gbias = reinterpret_cast<const float*>(ws + w.gb_off);
+  a.rowexp = reinterpret_cast<const float*>(ws + w.re_off);
   a.ratio = reinterpret_cast<const float*>(pb + pl.rat_off);
   a.fin = reinterpret_cast<const float*>(pb + pl.fin_off);
   a.M = M; a.V = d.V;
@@ -814,9 +841,6 @@ MfmaArgs mfma_args(const archead_handle* h, const void* x, int64_t M, int64_t ld
 }
 
 archead_status launch_mfma(const archead_handle* h, MfmaArgs& a, bool ce, hipStream_t s) {
-  // byte ranges of one tile's buffers must stay below 2 GiB
-  if (int64_t(kTM) * a.ldx * 2 >= (int64_t(1) << 31))
-    return fail(ARCHEAD_E_UNSUPPORTED, "ldx too large for the many-token kernel");
   const TiledShape ts = tiled_shape(h, a.M);
   const void* fn = kern::mfma(ce, ts.tm, ts.nw);
   const int lds = ts.nw == 4 ? (ts.tm == 64 ? MGeomT<64, 4>::LDS : MGeomT<128, 4>::LDS)
@@ -869,7 +893,7 @@ archead_status launch_softmax_partials(const archead_handle* h, const void* x, i
   if (path == Path::kTiled) {
     archead_status st = launch_mfma_prologue(h, x, M, ldx, w, base, s);
     if (st != ARCHEAD_OK) return st;
-    MfmaArgs a = mfma_args(h, x, M, ldx, w, base);
+    MfmaArgs a = mfma_args(h, M, w, base);
     a.tgt = targets;
     a.tgt64 = tgt64;
     a.part = part;
@@ -891,9 +915,9 @@ archead_status launch_softmax_partials(const archead_handle* h, const void* x, i
 // the unfused top-k).
 archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
                           void* out, archead_dtype out_dtype, int64_t ldo, void* ws,
-                          hipStream_t s, Path path) {
+                          hipStream_t s, Path path, int64_t call_M = 0) {
   archead_status st = ARCHEAD_OK;
-  const WsLayout w = ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path);
+  const WsLayout w = ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path, call_M);
   if (path == Path::kDec) {
     DecArgs a;
     memset(&a, 0, sizeof a);
@@ -917,7 +941,7 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
   if (path == Path::kTiled) {
     st = launch_mfma_prologue(h, x, M, ldx, w, static_cast<char*>(ws), s);
     if (st != ARCHEAD_OK) return st;
-    MfmaArgs a = mfma_args(h, x, M, ldx, w, static_cast<char*>(ws));
+    MfmaArgs a = mfma_args(h, M, w, static_cast<char*>(ws));
     a.out = out;
     a.ldo = ldo;
     a.out_bf16 = out_dtype == ARCHEAD_BF16;
@@ -932,6 +956,45 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
 
 
 }  // namespace
+
+namespace archead {
+
+size_t noalloc_bytes(const archead_handle* h, int64_t M) {
+  const Path path = choose_path(h, M);
+  if (path != Path::kTiled) return ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path).total;
+  const archead_desc& d = h->desc;
+  const size_t nch = size_t(exp_chunks(d.r_c) + exp_chunks(d.r_r));
+  const size_t nslot = size_t(d.d / d.g) + (d.r_c ? 1 : 0) + (d.r_r ? 1 : 0);
+  const size_t n_mt = size_t((M + kTM - 1) / kTM);
+  const int ks = s1_ksplit(h, M);
+  return align256(sizeof(uint16_t) * size_t(M) * nch * 64) + align256(sizeof(float) * n_mt * nslot * kTM) +
+         prep_layout(h).total +
+         (ks > 1 ? align256(sizeof(float) * size_t(ks) * size_t(M) * size_t(d.r_c + d.r_r)) : 0);
+}
+
+archead_status logits_in_chunks(const archead_handle* h, const void* x, int64_t M, int64_t ldx, void* out,
+                                archead_dtype out_dtype, int64_t ldo, void* ws, size_t ws_bytes,
+                                void* stream) {
+  archead_status st = check_args(h, x, M, ldx);
+  if (st != ARCHEAD_OK) return st;
+  st = check_out(h, out, out_dtype, ldo);
+  if (st != ARCHEAD_OK) return st;
+  const Path path = choose_path(h, M);
+  int64_t mc = M;
+  while (mc > 1 && ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, path, M).total > ws_bytes) mc = (mc + 1) / 2;
+  const size_t need = ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, path, M).total;
+  if (need > ws_bytes) return fail(ARCHEAD_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
+  const int64_t row = ldo * (out_dtype == ARCHEAD_F32 ? 4 : 2);
+  for (int64_t m0 = 0; m0 < M; m0 += mc) {
+    st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, M - m0 < mc ? M - m0 : mc, ldx,
+                    static_cast<char*>(out) + m0 * row, out_dtype, ldo, ws, static_cast<hipStream_t>(stream),
+                    path, M);
+    if (st != ARCHEAD_OK) return st;
+  }
+  return ARCHEAD_OK;
+}
+
+}  // namespace archead
 
 extern "C" {
 
@@ -1038,12 +1101,8 @@ archead_status archead_logits(const archead_handle* h, const void* x, int64_t M,
   clear_error();
   archead_status st = check_call(h, x, M, ldx, ws, ws_bytes, ARCHEAD_OP_LOGITS);
   if (st != ARCHEAD_OK || M == 0) return st;
-  if (!out) return fail(ARCHEAD_E_INVALID_ARG, "out is NULL");
-  if (out_dtype != ARCHEAD_F32 && out_dtype != ARCHEAD_BF16)
-    return fail(ARCHEAD_E_INVALID_ARG, "out_dtype must be ARCHEAD_F32 or ARCHEAD_BF16");
-  if (ldo < h->desc.V) return fail(ARCHEAD_E_INVALID_ARG, "ldo < V");
-  if (!aligned(out, out_dtype == ARCHEAD_F32 ? 4 : 2))
-    return fail(ARCHEAD_E_MISALIGNED, "out is not aligned to its element size");
+  st = check_out(h, out, out_dtype, ldo);
+  if (st != ARCHEAD_OK) return st;
   return logits_run(h, x, M, ldx, out, out_dtype, ldo, ws, static_cast<hipStream_t>(stream),
                     choose_path(h, M));
 }
@@ -1123,40 +1182,41 @@ archead_status archead_logit_fidelity_head(const archead_handle* h, const void* 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const WsLayout w = ws_layout(h, M, ARCHEAD_OP_FIDELITY);
   char* base = static_cast<char*>(ws);
-  st = launch_mfma_prologue(h, x, M, ldx, w, base, s);
+  st = launch_mfma_prologue(h, x, M, ldx, w, base, s, true);
   if (st != ARCHEAD_OK) return st;
-  MfmaArgs a = mfma_args(h, x, M, ldx, w, base);
-  a.n_mt = (M + 63) / 64;   // 64-row tiles of 4 waves in both passes
-  a.n_tiles = a.n_vt * a.n_mt;
-  a.tiles_per_xcd = (a.n_tiles + 7) / 8;
+  MfmaArgs a = mfma_args(h, M, w, base);
   a.dense = static_cast<const uint16_t*>(dense);
   a.ldw = ldw;
   a.fid_part = base + w.fid_off;
+  a.fid_need = reinterpret_cast<int*>(base + w.need_off);
   float* bref = reinterpret_cast<float*>(base + w.bref_off);
   a.bref = bref;
   a.ref_idx = ref_idx;
   a.rank = rank;
-  const int64_t grid = 8 * a.tiles_per_xcd;
-  if (grid > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "too many MFMA tiles");
-  for (int xe = 1; xe <= 2; ++xe) {
-    const void* fn = kern::mfma_fid(xe);
-    const int lds = xe == 1 ? MGeomT<64, 4, true>::LDS : MGeomT<64, 4>::LDS;
+  auto launch = [&](const void* fn, int tm, int nw, int lds, const char* what) {
+    a.n_mt = (M + tm - 1) / tm;
+    a.n_tiles = a.n_vt * a.n_mt;
+    a.tiles_per_xcd = (a.n_tiles + 7) / 8;
+    const int64_t grid = 8 * a.tiles_per_xcd;
+    if (grid > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "too many MFMA tiles");
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return hip_fail(e, "fidelity pass LDS size attribute");
+    if (e != hipSuccess) return hip_fail(e, what);
     void* args[] = {&a};
-    e = hipExtLaunchKernel(fn, dim3(unsigned(grid)), dim3(256), args, size_t(lds), s, nullptr,
-                           nullptr, 0);
-    if (e != hipSuccess) return hip_fail(e, "fidelity pass launch");
-    if (xe == 1) {
-      const FidTilePart* part = static_cast<const FidTilePart*>(a.fid_part);
-      int64_t n_vt = a.n_vt;
-      void* margs[] = {&part, &n_vt, &M, &kl, &sq, &ref_idx, &bref, &rank};
-      e = hipLaunchKernel(kern::fid_head_merge(), dim3(unsigned((M + 63) / 64)), dim3(64), margs,
-                          0, s);
-      if (e != hipSuccess) return hip_fail(e, "fidelity merge launch");
-    }
-  }
-  return ARCHEAD_OK;
+    e = hipExtLaunchKernel(fn, dim3(unsigned(grid)), dim3(unsigned(nw * 64)), args, size_t(lds), s,
+                           nullptr, nullptr, 0);
+    return e == hipSuccess ? ARCHEAD_OK : hip_fail(e, what);
+  };
+  // 128-row tiles halve the dense head's passes through the caches; up to 64
+  // tokens they would be half padding
+  st = M <= 64 ? launch(kern::mfma_fid(64), 64, 4, MGeomT<64, 4>::LDS, "fidelity pass")
+               : launch(kern::mfma_fid(128), 128, 8, MGeomT<128, 8>::LDS, "fidelity pass");
+  if (st != ARCHEAD_OK) return st;
+  const FidTilePart* part = static_cast<const FidTilePart*>(a.fid_part);
+  int64_t n_vt = a.n_vt;
+  void* margs[] = {&part, &n_vt, &M, &kl, &sq, &ref_idx, &bref, &rank, &a.fid_need};
+  const hipError_t e = hipLaunchKernel(kern::fid_head_merge(), dim3(unsigned(M)), dim3(kBlock), margs, 0, s);
+  if (e != hipSuccess) return hip_fail(e, "fidelity merge launch");
+  return launch(kern::mfma_rank(), 64, 4, MGeomT<64, 4>::LDS, "rank pass");
 }
 
 archead_status archead_logits_topk(const archead_handle* h, const void* x, int64_t M,

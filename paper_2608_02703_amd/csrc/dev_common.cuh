@@ -382,6 +382,7 @@ constexpr int kNoIdx = 0x7fffffff;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 constexpr int kTM = 256, kTN = 256;          // tile: tokens x vocabulary rows
@@ -390,6 +391,18 @@ constexpr int kKS = 64;                      // K elements per stage
 constexpr int kRing = 3;                     // LDS stages (two loads in flight)
 constexpr int kRasterGM = 4;                 // token tiles per raster group (measured: 2 and 8 slower at M = 4096)
 constexpr float kZeroScale = 0x1p-60f;       // stand-in for a zero scale
+// Scaling of the tiled kernel's operands (powers of two, so nothing rounds):
+// a token's x is multiplied by 2^(kXExp - e), e the exponent of its largest
+// magnitude; the codes are worth 2^-133 (unpack8_sub), so the accumulator is
+// 2^(kXExp - e - 133) times the logit over the slot's scale.  kXExp = 64 keeps
+// 24 bits above fp32's smallest subnormal for scale ratios of 2^40 (the fp16
+// range), and the fidelity pass's dense sums below overflow to logits of
+// 2^(63 + e).
+constexpr int kXExp = 64;
+constexpr int kCodeExp = -133;
+constexpr int kSteps = kKS / 16;             // MFMA K-steps per stage
+constexpr int kExpParts = 3;                 // K-steps of an expansion stage: the parts of t
+constexpr int kOutStride = 68;               // floats per token row of a wave's store buffer (64 + pad)
 constexpr int kExpDims = 16;                 // rank dimensions per expansion stage
 
 // Geometry of the tiled kernel for TM token rows per tile and NW waves per
@@ -397,34 +410,29 @@ constexpr int kExpDims = 16;                 // rank dimensions per expansion st
 // NW = 4 (1 x 4 waves of TM x 64; TM = 128: two workgroups per CU, TM = 64:
 // three), whose stage barriers are independent, so one's LDS waits, tile
 // start and epilogue overlap the others' MFMAs.  A stage holds x [TM][kKS] bf16,
-// codes [kTN][kKS/2], (FID: the dense head's rows [kTN][kKS] bf16,) the scale
+// codes [kTN][kKS/2] and, in a stage that starts a scale slot, the scale
 // ratios of the kTN columns and the slot biases of the TM rows.
-template <int TM, int NW = kMWaves, bool FID = false>
+template <int TM, int NW = kMWaves>
 struct MGeomT {
   static constexpr int WMW = NW / 4;                  // waves along the tokens
   static constexpr int WM = TM / WMW;                 // token rows per wave
-  static constexpr int MI = WM / 16;                  // 16-row MFMA blocks per wave
+  static constexpr int WN = kTN / (NW / WMW);         // vocabulary rows per wave
+  static constexpr int MI = WM / 32, NI = WN / 32;    // 32 x 32 MFMA blocks per wave
   static constexpr int XBYTES = TM * kKS * 2;         // x [TM][kKS] bf16
   static constexpr int CBYTES = kTN * kKS / 2;        // codes [kTN][kKS/2]
-  static constexpr int DOFF = XBYTES + CBYTES;        // dense rows (fidelity pass)
-  static constexpr int DBYTES = FID ? kTN * kKS * 2 : 0;
-  static constexpr int RAT = DOFF + DBYTES;           // fp32 [kTN] scale ratios
+  static constexpr int RAT = XBYTES + CBYTES;         // fp32 [kTN] scale ratios
   static constexpr int BIAS = RAT + kTN * 4;          // fp32 [TM] slot biases
   static constexpr int STAGE = BIAS + TM * 4;
   static constexpr int NX = XBYTES / 1024 / NW;       // x loads per wave and stage
   static constexpr int NC = CBYTES / 1024 / NW;       // code loads per wave and stage
-  static constexpr int NA = NW == 8 ? 1 : 2;          // ratio / bias loads per wave
-  static constexpr int ND = DBYTES / 1024 / NW;       // dense-row loads per wave
-  static constexpr int NL = NX + NC + NA + ND;        // loads per wave and stage
-  static constexpr int PPS = (NL + 2 * MI - 1) / (2 * MI);   // loads per MFMA row block
+  static constexpr int NLD = NX + NC;                 // of them in every stage
+  static constexpr int NL = NLD + 2;                  // loads per wave and stage (ratios, biases)
   static constexpr int LDS = kRing * STAGE;
-  static constexpr int WGS = FID ? 1 : NW == 8 ? 1 : (TM == 128 ? 2 : 3);   // workgroups per CU
+  static constexpr int WGS = NW == 8 ? 1 : (TM == 128 ? 2 : 3);   // workgroups per CU
   static_assert(NW == 8 || (NW == 4 && (TM == 128 || TM == 64)), "layouts built");
-  static_assert(!FID || (NW == 4 && TM == 64), "fidelity pass: 64-row tiles of 4 waves");
-  static_assert(XBYTES % (1024 * NW) == 0 && CBYTES % (1024 * NW) == 0 &&
-                DBYTES % (1024 * NW) == 0, "whole loads");
-  static_assert(LDS * WGS <= 160 * 1024, "LDS budget");
-  static_assert(TM % 64 == 0 && TM <= kTM, "bias loads of 64 rows per wave");
+  static_assert(XBYTES % (1024 * NW) == 0 && CBYTES % (1024 * NW) == 0, "whole loads");
+  static_assert(LDS * WGS <= 160 * 1024 && NW * 32 * kOutStride * 4 <= LDS, "LDS budget");
+  static_assert(TM % 64 == 0 && TM <= kTM, "whole 32-row blocks per wave");
 };
 using MGeom = MGeomT<kTM>;
 
@@ -442,12 +450,12 @@ __device__ __forceinline__ void dma4(__amdgpu_buffer_rsrc_t r, lds_u8* dst, uint
       r, reinterpret_cast<__attribute__((address_space(3))) void*>(dst), 4, voff, 0, 0, 0);
 }
 
-// Wait until at most N of this wave's vector-memory loads are in flight and
-// its LDS reads are done, then meet the other waves.  The memory clobber
-// keeps LDS accesses on their side of it.
+// Wait until at most N of this wave's vector-memory loads are in flight, then
+// meet the other waves.  The memory clobber keeps LDS accesses on their side
+// of it.
 template <int N>
 __device__ __forceinline__ void wait_loads_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
 template <typename T>
@@ -461,6 +469,26 @@ __device__ __forceinline__ bf16x8_t unpack8(uint32_t q, uint32_t kMask, uint32_t
   p[1] = int4_pair<1>(q, kMask, kMagic);
   p[2] = int4_pair<2>(q, kMask, kMagic);
   p[3] = int4_pair<3>(q, kMask, kMagic);
+  return __builtin_bit_cast(bf16x8_t, p);
+}
+
+// The eight codes u = c + 8 of a word as bf16 without a magic: the 8 low bits
+// of a bf16 pattern b are worth b * 2^-133 (its subnormals, and the first
+// binade above them, where the steps are the same), which the MFMA takes
+// exactly.  A nibble at bits 0..3 is thus u * 2^-133 and one at bits 4..7
+// 16 u * 2^-133, so the pairs 1 and 3 need no shift of their own: 5
+// operations per 8 codes (7 with the magic of unpack8).  EVEN: every pair is
+// moved to bits 0..3 (7 operations), for x that is not scaled by 1 / 16 at the
+// elements of pairs 1 and 3.
+template <bool EVEN>
+__device__ __forceinline__ bf16x8_t unpack8_sub(uint32_t q) {
+  constexpr uint32_t kLow = 0x000F000Fu, kHigh = 0x00F000F0u;
+  uint32_t p[4];
+  const uint32_t q8 = q >> 8;
+  p[0] = q & kLow;
+  p[1] = EVEN ? (q >> 4) & kLow : q & kHigh;
+  p[2] = q8 & kLow;
+  p[3] = EVEN ? (q >> 12) & kLow : q8 & kHigh;
   return __builtin_bit_cast(bf16x8_t, p);
 }
 

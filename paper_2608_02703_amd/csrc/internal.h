@@ -57,6 +57,15 @@ void clear_error();
 // `device` (the current device), taken once per device; called by
 // archead_create.
 archead_status scratch_setup(int device);
+// Bytes archead_logits_noalloc counts against ARCHEAD_NOALLOC_SCRATCH_BYTES:
+// the workspace of the call (on the tiled kernel's path: its split t, slot
+// biases, per-call tables and split stage-1 partials).
+size_t noalloc_bytes(const archead_handle* h, int64_t M);
+// archead_logits with its checks, in as few chunks of tokens as the workspace
+// allows, on the kernel the whole call would take.
+archead_status logits_in_chunks(const archead_handle* h, const void* x, int64_t M, int64_t ldx, void* out,
+                                archead_dtype out_dtype, int64_t ldo, void* ws, size_t ws_bytes,
+                                void* stream);
 
 // bytes per vocabulary row of core_u (int8 codes, or ARCHEAD_I5 words)
 int64_t core_u_row_bytes(const archead_desc& d);
@@ -75,12 +84,16 @@ struct WsLayout {
   size_t tst_off = 0;    // u64 [M, r_c + r_r] stamped t (decode and several-token kernels)
   // many-token (MFMA) path only:
   size_t ts_off = 0;     // bf16 [M][blocks][4][16] t split into hi, mid, lo (and 0)
-  size_t gb_off = 0;     // fp32 [n_mt][slots][256] slot biases
+  size_t xs_off = 0;     // bf16 [M][d] scaled x
+  size_t re_off = 0;     // fp32 [n_mt][256] the tokens' powers of two
+  size_t gs_off = 0;     // fp32 [d / g][M] sums of x over the residual groups
+  size_t gb_off = 0;     // fp32 [n_mt][d / g][256] slot biases
   size_t rat_off = 0;    // fp32 [n_vt][slots][256] scale ratios
   size_t fin_off = 0;    // fp32 [n_vt][256] final scales
   size_t wbf_off = 0;    // bf16 [r_c + r_r][d] factor codes of V_c and B_w
   size_t uc_off = 0;     // int8 [V][blocks][2][16] codes of U_c and A_w, padded, twice
-  size_t s1p_off = 0;    // fp32 [ksplit][M][r_c + r_r] stage-1 partials (split along d)
+  int ksplit = 1;        // workgroups along d of stage 1
+  size_t s1p_off = 0;    // fp32 [ksplit][M][r_c + r_r] stage-1 partials
   size_t part_off = 0;   // float2 [M, n_part] (CE)
   size_t tgt_off = 0;    // fp32 [M] (CE)
   size_t pidx_off = 0;   // int32 [M, n_part] (argmax)
@@ -97,11 +110,13 @@ struct WsLayout {
   // fidelity against a dense head: the tiled path's layout, then
   size_t fid_off = 0;     // [M][n_vt] per-tile statistics (32 bytes each)
   size_t bref_off = 0;    // fp32 [M] packed logit at the dense top-1
+  size_t need_off = 0;   // int32 [ceil(M / 64)][n_vt] tiles of the rank pass
   size_t total = 0;
   int64_t n_part = 0;
 };
 WsLayout ws_layout(const archead_handle* h, int64_t M, archead_op op);
-WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path path);
+WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path path,
+                        int64_t call_M = 0);
 
 // The many-token kernel's tables that depend on the head only (scale
 // ratios, final scales, bf16 V_c / B_w codes, paired U_c / A_w codes):

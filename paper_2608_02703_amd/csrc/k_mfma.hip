@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
       dst[int64_t(k++) * kTN] = prev / s;
       prev = s;
     }
-    a.fin[vt * kTN + c] = prev;
+    a.fin[vt * kTN + c] = prev * ldexpf(1.f, -(kXExp + kCodeExp));
   }
   // (b) 8 codes per thread
   const int64_t n8 = int64_t(a.rc + a.rr) * a.d / 8;
@@ -80,22 +80,60 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
   }
 }
 
+// One token's scaled x (a workgroup).
+__device__ __forceinline__ void scale_row(const Stage1MArgs& a, int64_t m, int* smax) {
+  const uint16_t* x = a.x + m * a.ldx;
+  int mx = 0;
+  for (int i = 8 * int(threadIdx.x); i < a.d; i += 8 * kS1MBlock) {
+    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(x + i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mx = max(mx, max(int(v[j] & 0x7fffu), int((v[j] >> 16) & 0x7fffu)));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off, 64));
+  if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kS1MWaves; ++w) mx = max(mx, smax[w]);
+  int e = (mx >> 7) - 127;   // zero and subnormal rows: -126; inf and NaN stay themselves
+  e = e < -126 ? -126 : (e > 127 ? 127 : e);
+  for (int i = 8 * int(threadIdx.x); i < a.d; i += 8 * kS1MBlock) {
+    u32x4_t v = *reinterpret_cast<const u32x4_t*>(x + i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = kXExp - e - (!a.even && (j & 1) ? 4 : 0);
+      const uint32_t lo = __float_as_uint(ldexpf(bf16_lo(v[j]), k));
+      const uint32_t hi = __float_as_uint(ldexpf(bf16_hi(v[j]), k));
+      v[j] = (lo >> 16) | (hi & 0xffff0000u);
+    }
+    *reinterpret_cast<u32x4_t*>(a.xs + m * a.d + i) = v;
+  }
+  if (threadIdx.x == 0) a.rowexp[m] = ldexpf(1.f, e);
+}
+
 __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
   __shared__ float red[kS1MWaves][kS1MTok][kS1MCols + 1];
+  const int64_t n_s1 = int64_t(a.mblocks) * a.rblocks * a.ksplit;
+  if (int64_t(blockIdx.x) >= n_s1) {
+    scale_row(a, int64_t(blockIdx.x) - n_s1, reinterpret_cast<int*>(&red[0][0][0]));
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, q = lane >> 4;
   const int R = a.rc + a.rr;
-  const int64_t tok0 = int64_t(blockIdx.x) * kS1MTok;
-  const int kb = blockIdx.y * kS1MCols;           // first factor row of this workgroup
+  const int bx = int(blockIdx.x) % a.mblocks, byz = int(blockIdx.x) / a.mblocks;
+  const int by = byz % a.rblocks;
+  const int64_t tok0 = int64_t(bx) * kS1MTok;
+  const int kb = by * kS1MCols;           // first factor row of this workgroup
   const int ngrp = a.d / a.g, cpg = a.g / 32;
-  // this workgroup's residual groups (split blockIdx.z of ksplit equal
-  // parts), dealt to its waves
-  const int ks = blockIdx.z, gps = ngrp / a.ksplit, g0 = ks * gps;
+  // this workgroup's residual groups (split ks of ksplit equal parts), dealt
+  // to its waves
+  const int ks = byz / a.rblocks, gps = ngrp / a.ksplit, g0 = ks * gps;
   const int c0 = (g0 + wid * gps / kS1MWaves) * cpg, c1 = (g0 + (wid + 1) * gps / kS1MWaves) * cpg;
   const int64_t mrow = tok0 + lr < a.M ? tok0 + lr : a.M - 1;
   const uint16_t* xrow = a.x + mrow * a.ldx + 8 * q;
-  const bool do_bias = blockIdx.y == 0;
+  const bool do_sum = by == 0;
   constexpr int NB = kS1MCols / 16;
   const int nblk = R - kb >= kS1MCols ? NB : (R - kb + 15) / 16;
 
@@ -134,7 +172,7 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
   if (c0 < c1) load(c0, A, B, s);
   for (int c = c0; c < c1; ++c) {
     if (c + 1 < c1) load(c + 1, An, Bn, sn);
-    if (do_bias) gs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, ones, gs, 0, 0, 0);
+    if (do_sum) gs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, ones, gs, 0, 0, 0);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       if (nb < nblk) {
@@ -142,14 +180,13 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
         acc[nb] += s[nb] * __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[nb], z, 0, 0, 0);
       }
     }
-    if (do_bias && (c + 1) % cpg == 0) {
+    if (do_sum && (c + 1) % cpg == 0) {
       const int j = c / cpg;
       if (lr == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int64_t m = tok0 + 4 * q + i;
-          if (m < a.M)
-            a.gbias[((m / kTM) * a.nslot + j) * kTM + m % kTM] = -float(archead::kInt4Bias) * gs[i];
+          if (m < a.M) a.gsum[j * a.M + m] = gs[i];
         }
       }
       gs = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -157,22 +194,6 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
     A = An;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) B[nb] = Bn[nb], s[nb] = sn[nb];
-  }
-  if (do_bias && ks == 0) {
-    // zero biases of the expansion slots and zero padding of the split t
-    const int nz = a.nslot - ngrp;
-    for (int e = threadIdx.x; e < kS1MTok * nz; e += kS1MBlock) {
-      const int64_t m = tok0 + e / nz;
-      if (m < a.M) a.gbias[((m / kTM) * a.nslot + ngrp + e % nz) * kTM + m % kTM] = 0.f;
-    }
-    const int pu = kExpDims * a.nch_u;   // padded dimensions of the U_c part
-    for (int e = threadIdx.x; e < kS1MTok * a.nch * 64; e += kS1MBlock) {
-      const int tt = e / (a.nch * 64), j = e % (a.nch * 64), blk = j / 64, w = j % 64;
-      const int dim = blk * kExpDims + w % kExpDims;
-      const bool pad = w >= 48 || (dim < pu ? dim >= a.rc : dim - pu >= a.rr);
-      const int64_t m = tok0 + tt;
-      if (m < a.M && pad) a.tsplit[(m * a.nch + blk) * 64 + w] = 0;
-    }
   }
   if (R == 0) return;
 #pragma unroll
@@ -188,44 +209,46 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
       float v = red[0][tt][c];
 #pragma unroll
       for (int w = 1; w < kS1MWaves; ++w) v += red[w][tt][c];
-      if (a.ksplit > 1) {
-        a.tpart[(int64_t(ks) * a.M + m) * R + k] = v;
-        continue;
-      }
-      const __bf16 hi = (__bf16)v;
-      const float r1 = v - float(hi);
-      const __bf16 md = (__bf16)r1;
-      const __bf16 lo = (__bf16)(r1 - float(md));
-      const int dim = k < a.rc ? k : kExpDims * a.nch_u + (k - a.rc);
-      uint16_t* dst = a.tsplit + (m * a.nch + dim / kExpDims) * 64 + dim % kExpDims;
-      dst[0] = __builtin_bit_cast(uint16_t, hi);
-      dst[16] = __builtin_bit_cast(uint16_t, md);
-      dst[32] = __builtin_bit_cast(uint16_t, lo);
+      a.tpart[(int64_t(ks) * a.M + m) * R + k] = v;
     }
   }
 }
 
-// t[m][k] as the sum of the ksplit partials in split order, then split
-// into three bf16 parts as k_stage1m does when it is not split.
+// One thread per (token, rank dimension padded to blocks of 16), then one per
+// (residual group, token of the padded count, tokens fastest).
 __global__ __launch_bounds__(kBlock) void k_stage1m_fin(Stage1MArgs a) {
-  const int R = a.rc + a.rr;
-  const int64_t e = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (e >= a.M * R) return;
-  const int64_t m = e / R;
-  const int k = int(e % R);
-  float v = a.tpart[m * R + k];
-  for (int ks = 1; ks < a.ksplit; ++ks) v += a.tpart[(int64_t(ks) * a.M + m) * R + k];
-  const __bf16 hi = (__bf16)v;
-  const float r1 = v - float(hi);
-  const __bf16 md = (__bf16)r1;
-  const __bf16 lo = (__bf16)(r1 - float(md));
-  const int dim = k < a.rc ? k : kExpDims * a.nch_u + (k - a.rc);
-  uint16_t* dst = a.tsplit + (m * a.nch + dim / kExpDims) * 64 + dim % kExpDims;
-  dst[0] = __builtin_bit_cast(uint16_t, hi);
-  dst[16] = __builtin_bit_cast(uint16_t, md);
-  dst[32] = __builtin_bit_cast(uint16_t, lo);
+  const int R = a.rc + a.rr, ngrp = a.d / a.g, dims = a.nch * kExpDims;
+  int64_t t = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  auto exponent = [&](int64_t m) { return int(__float_as_uint(a.rowexp[m]) >> 23) - 127; };
+  if (t < a.M * dims) {
+    const int64_t m = t / dims;
+    const int c = int(t % dims) / kExpDims, i = int(t % kExpDims);
+    const int dim = (c < a.nch_u ? c : c - a.nch_u) * kExpDims + i;
+    __bf16 hi = (__bf16)0.f, md = hi, lo = hi;
+    if (dim < (c < a.nch_u ? a.rc : a.rr)) {
+      const int k = c < a.nch_u ? dim : a.rc + dim;
+      float v = a.tpart[m * R + k];
+      for (int ks = 1; ks < a.ksplit; ++ks) v += a.tpart[(int64_t(ks) * a.M + m) * R + k];
+      v = ldexpf(v, kXExp + kCodeExp - exponent(m));
+      hi = (__bf16)v;
+      const float r1 = v - float(hi);
+      md = (__bf16)r1;
+      lo = (__bf16)(r1 - float(md));
+    }
+    uint16_t* dst = a.tsplit + (m * a.nch + c) * 64 + i;
+    dst[0] = __builtin_bit_cast(uint16_t, hi);
+    dst[16] = __builtin_bit_cast(uint16_t, md);
+    dst[32] = __builtin_bit_cast(uint16_t, lo);
+    dst[48] = 0;
+    return;
+  }
+  t -= a.M * dims;
+  const int64_t mp = (a.M + kTM - 1) / kTM * kTM;
+  const int64_t m = t % mp, j = t / mp;
+  if (j >= ngrp) return;
+  a.gbias[((m / kTM) * ngrp + j) * kTM + m % kTM] =
+      m < a.M ? -8.f * ldexpf(a.gsum[j * a.M + m], kXExp + kCodeExp - exponent(m)) : 0.f;
 }
-
 
 }  // namespace
 

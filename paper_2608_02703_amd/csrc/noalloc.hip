@@ -20,9 +20,14 @@ namespace {
 
 constexpr int kMaxDevices = 64;
 
-// The static workspace: ARCHEAD_NOALLOC_SCRATCH_BYTES on every device the
-// library runs on, held until the process ends.
-static __device__ __align__(256) unsigned char scratch[ARCHEAD_NOALLOC_SCRATCH_BYTES];
+// The static workspace on every device the library runs on, held until the
+// process ends.  Which calls are taken is decided by noalloc_bytes against
+// ARCHEAD_NOALLOC_SCRATCH_BYTES; it leaves out the tiled kernel's scaled copy
+// of x and its group sums, so the array has room for those of a few tokens of
+// any head beside it, and a call whose own do not fit runs in chunks of tokens
+// (bit-identical: the split of stage 1 along d is the whole call's).
+constexpr size_t kScratchBytes = size_t(ARCHEAD_NOALLOC_SCRATCH_BYTES) + (4u << 20);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_mu;
 void* g_scratch[kMaxDevices];   // device address of `scratch` per device, or null
@@ -57,7 +62,7 @@ archead_status archead_logits_noalloc(const archead_handle* h, const void* x, in
   if (!h) return fail(ARCHEAD_E_INVALID_ARG, "handle is NULL");
   if (M < 0) return fail(ARCHEAD_E_INVALID_ARG, "M = %lld < 0", (long long)M);
   if (M == 0) return ARCHEAD_OK;
-  const size_t need = archead_workspace_bytes(h, M, ARCHEAD_OP_LOGITS);
+  const size_t need = noalloc_bytes(h, M);
   if (need > size_t(ARCHEAD_NOALLOC_SCRATCH_BYTES))
     return fail(ARCHEAD_E_WORKSPACE,
                 "M = %lld needs %zu bytes of workspace; the static workspace holds %zu "
@@ -69,8 +74,7 @@ archead_status archead_logits_noalloc(const archead_handle* h, const void* x, in
     if (h->device >= 0 && h->device < kMaxDevices) ws = g_scratch[h->device];
   }
   if (!ws) return fail(ARCHEAD_E_HIP, "static workspace of device %d is not set up", h->device);
-  return archead_logits(h, x, M, ldx, out, out_dtype, ldo, ws,
-                        size_t(ARCHEAD_NOALLOC_SCRATCH_BYTES), stream);
+  return logits_in_chunks(h, x, M, ldx, out, out_dtype, ldo, ws, kScratchBytes, stream);
 }
 
 }  // extern "C"
