@@ -318,18 +318,10 @@ bool topk_fused(const archead_handle* h, int64_t M) {
                          gemv_mode(h).gen) != nullptr;
 }
 
-// Slices per token row of the top-k of a chunk of logits: enough that the
-// chunk's rows give about a thousand workgroups, at most 64.
-int64_t topk_row_parts(int64_t chunk) {
-  const int64_t np = (1024 + chunk - 1) / chunk;
-  return np < 1 ? 1 : (np > 64 ? 64 : np);
-}
-
 static WsLayout topk_layout(const archead_handle* h, int64_t M) {
   WsLayout w;
   const archead_desc& d = h->desc;
   size_t off = 0;
-  int64_t rows = 1;
   if (topk_fused(h, M)) {
     w = ws_layout(h, 1, ARCHEAD_OP_LOGITS);   // the GEMV's stage-1 words
     off = w.total;
@@ -350,10 +342,15 @@ static WsLayout topk_layout(const archead_handle* h, int64_t M) {
       inner = t > inner ? t : inner;
     }
     off = align256(off + inner);
-    w.n_part = topk_row_parts(chunk);
-    rows = chunk;
+    int64_t cs = kTopKChunkUnit;
+    while ((d.V + cs - 1) / cs > kTopKChunks) cs *= 2;
+    w.tk_cs = int(cs);
+    w.tk_n_chunk = int((d.V + cs - 1) / cs);
+    w.tk_key_off = off;
+    w.total = align256(off + sizeof(uint32_t) * size_t(chunk) * size_t(w.tk_n_chunk));
+    return w;
   }
-  const size_t lists = size_t(rows) * size_t(w.n_part) * kTopKMaxK;
+  const size_t lists = size_t(w.n_part) * kTopKMaxK;
   w.tk_pv_off = off;
   off = align256(off + sizeof(float) * lists);
   w.tk_pi_off = off;
@@ -1234,11 +1231,11 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
   hipStream_t s = static_cast<hipStream_t>(stream);
   const WsLayout w = ws_layout(h, M, ARCHEAD_OP_TOPK);
   char* base = static_cast<char*>(ws);
-  float* pv = reinterpret_cast<float*>(base + w.tk_pv_off);
-  int* pi = reinterpret_cast<int*>(base + w.tk_pi_off);
-  int64_t np = w.n_part;
   hipError_t e;
   if (w.tk_fused) {
+    float* pv = reinterpret_cast<float*>(base + w.tk_pv_off);
+    int* pi = reinterpret_cast<int*>(base + w.tk_pi_off);
+    int64_t np = w.n_part;
     GemvArgs a = gemv_args(h, x, ldx, reinterpret_cast<uint64_t*>(base + w.tst_off));
     a.tk_val = pv;
     a.tk_idx = pi;
@@ -1252,24 +1249,24 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
   }
   const int64_t V = h->desc.V;
   float* lg = reinterpret_cast<float*>(base + w.tk_lg_off);
-  // slices of whole 64-logit steps
-  int64_t slice = (V + np - 1) / np;
-  slice = (slice + 63) / 64 * 64;
   for (int64_t m0 = 0; m0 < M; m0 += w.tk_chunk) {
     const int64_t mc = M - m0 < w.tk_chunk ? M - m0 : w.tk_chunk;
     st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, mc, ldx, lg, ARCHEAD_F32, V,
                     base + w.tk_in_off, s, w.tk_path);
     if (st != ARCHEAD_OK) return st;
     int64_t ldl = V;
-    void* rargs[] = {&lg, &ldl, const_cast<int64_t*>(&V), &k, &slice, &pv, &pi};
-    e = hipLaunchKernel(kern::topk_rows(), dim3(unsigned(np), unsigned(mc)), dim3(kBlock), rargs,
-                        0, s);
-    if (e != hipSuccess) return hip_fail(e, "top-k rows launch");
+    uint32_t* keys = reinterpret_cast<uint32_t*>(base + w.tk_key_off);
+    int cs = w.tk_cs, nc = w.tk_n_chunk;
+    constexpr int kPerWg = kWaves * kTopKWaveChunks;
+    void* xargs[] = {&lg, &ldl, const_cast<int64_t*>(&V), &cs, &nc, &keys};
+    e = hipLaunchKernel(kern::topk_max(), dim3(unsigned((nc + kPerWg - 1) / kPerWg), unsigned(mc)),
+                        dim3(kBlock), xargs, 0, s);
+    if (e != hipSuccess) return hip_fail(e, "top-k chunk maxima launch");
     float* vo = vals ? vals + m0 * ldk : nullptr;
     int64_t* io = idx + m0 * ldk;
-    void* margs[] = {&pv, &pi, &np, &k, &vo, &io, &ldk};
-    e = launch_topk_merge(np, k, mc, margs, s);
-    if (e != hipSuccess) return hip_fail(e, "top-k merge launch");
+    void* sargs[] = {&lg, &ldl, const_cast<int64_t*>(&V), &cs, &nc, &keys, &k, &vo, &io, &ldk};
+    e = hipLaunchKernel(kern::topk_select(), dim3(unsigned(mc)), dim3(kTopKChunks), sargs, 0, s);
+    if (e != hipSuccess) return hip_fail(e, "top-k selection launch");
   }
   return ARCHEAD_OK;
 }

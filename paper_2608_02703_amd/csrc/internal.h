@@ -47,6 +47,10 @@ constexpr int kMidWindow = 256;           // elements of d per x window of that 
 constexpr int kMidWaveCount = 8;          // its waves per workgroup
 constexpr int kTopKMaxK = 64;             // largest k of archead_logits_topk (lanes of a wave)
 constexpr int64_t kTopKChunk = 256;       // tokens per chunk of the unfused top-k
+// the unfused top-k's chunks of a row of logits: at most kTopKChunks, of a
+// power of two times kTopKChunkUnit logits; a wave of the first kernel takes
+// kTopKWaveChunks
+constexpr int kTopKChunks = 1024, kTopKChunkUnit = 256, kTopKWaveChunks = 4;
 constexpr int kTopKMergeBlock = 1024;     // threads of the round-based top-k merge workgroup
 constexpr int kTopKMergeC = 8;            // candidates per thread of that merge (else the scan merge)
 
@@ -104,8 +108,10 @@ struct WsLayout {
   int64_t tk_chunk = 0;   // tokens per chunk (unfused)
   size_t tk_lg_off = 0;   // fp32 [chunk][V]
   size_t tk_in_off = 0;   // workspace of the chunk's logits call
-  size_t tk_pv_off = 0;   // fp32 [chunk or 1][n_part][kTopKMax] partial lists
+  size_t tk_pv_off = 0;   // fused: fp32 [n_part][kTopKMax] partial lists
   size_t tk_pi_off = 0;   // int32, the same shape
+  size_t tk_key_off = 0;  // unfused: uint32 [chunk][tk_n_chunk] order keys of the rows' chunk maxima
+  int tk_cs = 0, tk_n_chunk = 0;   // logits per chunk of a row, chunks
   Path tk_path = Path::kGemv;   // kernel of the chunks' logits (that of the whole M)
   // fidelity against a dense head: the tiled path's layout, then
   size_t fid_off = 0;     // [M][n_vt] per-tile statistics (32 bytes each)

@@ -1,6 +1,6 @@
 // Top-k selection: the single-token decode GEMV with the fused top-k
-// epilogue, the top-k of rows of fp32 logits, and the merge of per-partial
-// lists.  Every list is in the order of the first-index argmax (larger value
+// epilogue and the merge of its per-partial lists, and the top-k of rows of
+// fp32 logits.  Every list is in the order of the first-index argmax (larger value
 // first, equal values by smaller index), so the merged result is the first k
 // entries of the stable descending sort of the token's logits.
 #include "dev_gemv.cuh"
@@ -83,72 +83,165 @@ __device__ __forceinline__ void tk_row16_best(float& v, int& i) {
   tk_pick_dpp<0x140>(v, i);
 }
 
-// Per (partial p, token m) of grid (n_part, M): the k best pairs of
-// logits[m, v] over the slice v in [p * slice, min(V, (p + 1) * slice)),
-// into pv / pi [M][n_part][k].
-//  * For k <= 16, a floor first: each lane's best logit of the slice (its
-//    share: v = lo + tid, lo + tid + kBlock, ...), then k rounds of the
-//    wave's best among those (the owner drops it after each): the k-th is
-//    ranked at or below the wave's own k-th best (k lanes hold one at least
-//    as good), so the wave's list only sees candidates at or above it.
-//  * The four wave lists then merge by rank (distinct indices: every entry
-//    has a distinct rank), not by inserting one list into another.
-__global__ __launch_bounds__(kBlock) void k_topk_rows(const float* logits, int64_t ldl, int64_t V,
-                                                      int k, int64_t slice, float* pv, int* pi) {
-  __shared__ float sv[kWaves * 64];
-  __shared__ int si[kWaves * 64];
+// ------------------------------------------------ top-k of rows of logits
+// Two launches.  k_topk_max writes the largest logit of every chunk of a row
+// (as an order key); the k-th largest of a row's chunk maxima is a floor for
+// its k-th largest logit, so k_topk_select reads again only the chunks whose
+// maximum reaches the floor (k of them, but for ties) and ranks the few logits
+// at or above it.  What bounds it: the first launch reads the logits once, from
+// the caches for the usual sizes; the second is a chain of short steps of one
+// workgroup per token.  24 tokens of 128256 logits, k = 50: 5.5 + 9.3 us
+// (sorted lists per slice and a merge in k rounds: 61 + 52 us).
+//
+// Order key of a logit: larger for larger values, equal for equal ones (0 and
+// -0), 0 for NaN (which is never selected).
+__device__ __forceinline__ uint32_t tk_key(float v) {
+  const uint32_t u = __float_as_uint(v + 0.f);   // -0 becomes 0
+  return v != v ? 0u : (u & 0x80000000u ? ~u : u | 0x80000000u);
+}
+
+constexpr int kChunkUnit = 256;          // logits a wave takes at a time
+constexpr int kSelBlock = 1024, kSelWaves = kSelBlock / 64;
+constexpr int kSelCand = 2048;           // candidates held; more take the list scan
+constexpr int kMaxWaveChunks = 4;        // chunks per wave of k_topk_max
+static_assert(archead::kTopKChunks == kSelBlock && archead::kTopKChunkUnit == kChunkUnit &&
+              archead::kTopKWaveChunks == kMaxWaveChunks, "host and kernels agree on the chunks");
+
+// Grid (ceil(n_chunk / (kWaves kMaxWaveChunks)), tokens): keys[m][c] = the
+// largest key of logits [c cs, (c + 1) cs) of row m.
+__global__ __launch_bounds__(kBlock) void k_topk_max(const float* logits, int64_t ldl, int64_t V, int cs,
+                                                     int n_chunk, uint32_t* keys) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int64_t m = blockIdx.y;
+  const float* row = logits + m * ldl;
+  const int c0 = (int(blockIdx.x) * kWaves + wid) * kMaxWaveChunks;
+  uint32_t best[kMaxWaveChunks] = {};
+  for (int o = 0; o < cs; o += kChunkUnit) {
+    float v[kMaxWaveChunks][4];
+#pragma unroll
+    for (int c = 0; c < kMaxWaveChunks; ++c)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t j = int64_t(c0 + c) * cs + o + 64 * u + lane;
+        v[c][u] = j < V ? row[j] : NAN;
+      }
+#pragma unroll
+    for (int c = 0; c < kMaxWaveChunks; ++c)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) best[c] = max(best[c], tk_key(v[c][u]));
+  }
+#pragma unroll
+  for (int c = 0; c < kMaxWaveChunks; ++c) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) best[c] = max(best[c], uint32_t(__shfl_xor(int(best[c]), off, 64)));
+    if (lane == 0 && c0 + c < n_chunk) keys[m * n_chunk + c0 + c] = best[c];
+  }
+}
+
+// Grid tokens: the k best of row m in order, out to vals[m * ldk + j] (may be
+// null) and idx[m * ldk + j], j < k; a slot no value reached (fewer than k
+// non-NaN logits) gets (-inf, -1).  n_chunk <= kSelBlock.
+__global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, int64_t ldl, int64_t V, int cs,
+                                                           int n_chunk, const uint32_t* keys, int k,
+                                                           float* vals, int64_t* idx, int64_t ldk) {
+  __shared__ uint32_t skey[kSelBlock];
+  __shared__ int slist[kSelBlock];
+  __shared__ float cval[kSelCand];
+  __shared__ int cidx[kSelCand];
   __shared__ float ov[kTopKMax];
   __shared__ int oi[kTopKMax];
+  __shared__ uint32_t sfloor;
+  __shared__ int nlist, ncand;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-  const int64_t m = blockIdx.y, p = blockIdx.x, n_part = gridDim.x;
-  const int64_t lo = p * slice;
-  const int64_t hi = lo + slice < V ? lo + slice : V;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m = blockIdx.x;
   const float* row = logits + m * ldl;
-  float fv = -INFINITY;
-  int fi = kNoIdx;
-  if (k <= 16) {
-    float cv = -INFINITY;
-    int ci = kNoIdx;
-    for (int64_t j0 = lo + tid; j0 < hi; j0 += int64_t(kScanBatch) * kBlock) {
-      float v[kScanBatch];
+  const uint32_t mine = tid < n_chunk ? keys[m * n_chunk + tid] : 0u;
+  skey[tid] = mine;
+  if (tid == 0) {
+    nlist = 0;
+    ncand = 0;
+  }
+  __syncthreads();
+  if (wid == 0) {
+    // the largest key prefix of 20 bits that at least k chunk maxima reach
+    // (the low bits only decide how many more chunks are read)
+    uint32_t kk[kSelWaves];
 #pragma unroll
-      for (int u = 0; u < kScanBatch; ++u) {
-        const int64_t j = j0 + int64_t(u) * kBlock;
-        v[u] = j < hi ? row[j] : -INFINITY;
-      }
+    for (int i = 0; i < kSelWaves; ++i) kk[i] = skey[64 * i + lane];
+    uint32_t f = 0;
+    for (int bit = 31; bit >= 12; --bit) {
+      const uint32_t t = f | (1u << bit);
+      int n = 0;
 #pragma unroll
-      for (int u = 0; u < kScanBatch; ++u) {
-        const int64_t j = j0 + int64_t(u) * kBlock;
-        if (j < hi) tk_pick(cv, ci, v[u], int(j));
-      }
+      for (int i = 0; i < kSelWaves; ++i) n += __popcll(__ballot(kk[i] >= t));
+      if (n >= k) f = t;
     }
-    for (int r = 0; r < k; ++r) {
-      float gv = cv;
-      int gi = ci;
-      tk_row16_best(gv, gi);
-      float bv = rlane_f(gv, 0);
-      int bi = __builtin_amdgcn_readlane(gi, 0);
+    if (lane == 0) sfloor = f ? f : 1u;   // 1: every logit but NaN
+  }
+  __syncthreads();
+  const uint32_t fl = sfloor;
+  if (mine >= fl) slist[atomicAdd(&nlist, 1)] = tid;
+  __syncthreads();
+  const int upc = cs / kChunkUnit, units = nlist * upc;
+  constexpr int kBatch = 4;   // units of a wave in flight
+  for (int u0 = wid; u0 < units; u0 += kBatch * kSelWaves) {
+    float v[kBatch][4];
+    int64_t j0[kBatch];
 #pragma unroll
-      for (int rr = 1; rr < 4; ++rr)
-        tk_pick(bv, bi, rlane_f(gv, 16 * rr), __builtin_amdgcn_readlane(gi, 16 * rr));
-      fv = bv;
-      fi = bi;
-      if (bi != kNoIdx && ci == bi) {
-        cv = -INFINITY;
-        ci = kNoIdx;
+    for (int b = 0; b < kBatch; ++b) {
+      const int u = u0 + b * kSelWaves;
+      const bool on = u < units;
+      j0[b] = on ? int64_t(slist[u / upc]) * cs + int64_t(u % upc) * kChunkUnit + lane : V;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[b][q] = j0[b] + 64 * q < V ? row[j0[b] + 64 * q] : NAN;
+    }
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool hit = tk_key(v[b][q]) >= fl;
+        const uint64_t mask = __ballot(hit);
+        if (!mask) continue;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&ncand, __popcll(mask));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((uint64_t(1) << lane) - 1));
+        if (hit && at < kSelCand) {
+          cval[at] = v[b][q];
+          cidx[at] = int(j0[b] + 64 * q);
+        }
       }
+  }
+  __syncthreads();
+  const int nc = ncand;
+  if (nc > kSelCand) {
+    // (many logits tied at the floor) sorted lists over the whole row, one per
+    // wave, merged by rank
+    float lv = -INFINITY, bv = -INFINITY;
+    int li = kNoIdx, bi = kNoIdx;
+    for (int64_t j = tid; j - lane < V; j += kSelBlock)
+      tk_offer(lv, li, bv, bi, j < V ? row[j] : NAN, int(j), j < V, lane, k);
+    tk_rank_merge<kSelWaves>(lv, li, tid, k, cval, cidx, ov, oi);
+    if (tid < k) {
+      if (vals) vals[m * ldk + tid] = ov[tid];
+      idx[m * ldk + tid] = oi[tid] == kNoIdx ? int64_t(-1) : int64_t(oi[tid]);
+    }
+    return;
+  }
+  // rank each candidate among all (distinct indices: distinct ranks)
+  for (int t = tid; t < nc; t += kSelBlock) {
+    const float v = cval[t];
+    const int i = cidx[t];
+    int rank = 0;
+    for (int o = 0; o < nc; ++o) rank += tk_better(cval[o], cidx[o], v, i);
+    if (rank < k) {
+      if (vals) vals[m * ldk + rank] = v;
+      idx[m * ldk + rank] = int64_t(i);
     }
   }
-  float lv = -INFINITY, bv = -INFINITY;
-  int li = kNoIdx, bi = kNoIdx;
-  tk_scan(lo, hi, [&](int64_t j) { return row[j]; }, [&](int64_t j) { return int(j); }, lane, wid,
-          k, lv, li, bv, bi, fv, fi);
-  tk_rank_merge<kWaves>(lv, li, tid, k, sv, si, ov, oi);
-  if (tid < k) {
-    const int64_t o = (m * n_part + p) * k + tid;
-    pv[o] = ov[tid];
-    pi[o] = oi[tid];
+  if (tid >= nc && tid < k) {
+    if (vals) vals[m * ldk + tid] = -INFINITY;
+    idx[m * ldk + tid] = -1;
   }
 }
 
@@ -284,7 +377,8 @@ const void* gemv_topk(int lpr, bool sc8, int gen) {
   return gemv_topk_fn<0>(lpr, sc8);
 }
 
-const void* topk_rows() { return reinterpret_cast<const void*>(k_topk_rows); }
+const void* topk_max() { return reinterpret_cast<const void*>(k_topk_max); }
+const void* topk_select() { return reinterpret_cast<const void*>(k_topk_select); }
 const void* topk_merge(int block) {
   return block == 256 ? reinterpret_cast<const void*>(k_topk_merge<256>)
                       : reinterpret_cast<const void*>(k_topk_merge<1024>);

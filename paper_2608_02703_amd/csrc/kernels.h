@@ -12,10 +12,11 @@ namespace kern {
 // with ARCHEAD_I5 core-left codes; 1 and 2 only for lpr 8 and 16, else null)
 const void* gemv(int tok, int lpr, bool ce, bool sc8, int gen);
 // the single-token GEMV with the fused top-k epilogue (k_gemv<1, LPR, false,
-// SC8, GEN, true>; null where gemv has no such variant), the top-k of rows
-// of fp32 logits and the merge of per-partial top-k lists
+// SC8, GEN, true>; null where gemv has no such variant), the merge of its
+// per-workgroup lists, and the top-k of rows of fp32 logits in two kernels
 const void* gemv_topk(int lpr, bool sc8, int gen);
-const void* topk_rows();
+const void* topk_max();      // the maxima of the rows' chunks, then
+const void* topk_select();   // the k best from the chunks that can hold one
 const void* topk_merge(int block);   // k rounds; workgroups of 256 or kTopKMergeBlock threads, kTopKMergeC candidates each
 const void* topk_merge_scan();   // any number of candidates
 // MFMA decode kernel k_dec<GW, CE, EK, SC8, GEN>: gw = g / 32 code words per

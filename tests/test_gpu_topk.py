@@ -162,3 +162,48 @@ def test_topk_argument_checks():
         assert ab.TOPK_MAX == 64
     finally:
         ph.close()
+
+
+@pytest.mark.parametrize("V", [70, 255, 1025, 5000])
+def test_topk_chunk_edges(V):
+    """Rows of less than k chunks of 256 logits, of exactly some chunks and one
+    more; logits equal in many chunks (more ties than the candidate buffer
+    holds), signed zeros, infinities, NaN, and fewer than k numbers in a row."""
+    from paper_2608_02703_amd import PackedHead
+    # one group, no factors: logit[m, v] = scale[v] * (code row 0) . x[m]
+    h = make_head("tiny", V=V, d=64, g=64, rc=0, rr=0)
+    rng = np.random.default_rng(V)
+    h.res_codes[:] = h.res_codes[0]
+    h.res_scales[:, 0] = rng.integers(1, 40, V) / 16.0   # many ties
+    h.res_scales[V // 2, 0] = np.float16(np.nan)
+    h.res_scales[V - 1, 0] = np.float16(np.inf)
+    x = make_x("tiny", 5, d=64)
+    x[3] = 0                                             # every logit 0 (NaN where the scale is not finite)
+    x[4, :] = 0x7F80                                     # NaN rows: nothing to select
+    for const in (False, True):
+        if const:
+            h.res_scales[:] = 0.5                        # all logits of a row equal
+        ph = PackedHead.from_arrays(h)
+        try:
+            for path in ("gemv", "mid", "tiled"):
+                if path == "mid" and (V < 1024):
+                    continue
+                ph.force_path(path)
+                for k in (1, 16, 17, 50, 64):
+                    say(f"top-k chunk edges V={V} {path} k={k} const={const}")
+                    xt = torch_x(x)
+                    lg = ph.logits(xt)
+                    vals, idx = ph.logits_topk(xt, k)
+                    torch.cuda.synchronize()
+                    lg, vals, idx = lg.cpu().numpy(), vals.cpu().numpy(), idx.cpu().numpy()
+                    for m in range(5):
+                        ok = np.nonzero(~np.isnan(lg[m]))[0]
+                        order = ok[np.argsort(-lg[m, ok], kind="stable")][:k]
+                        want = np.full(k, -1)
+                        want[:order.size] = order
+                        assert np.array_equal(idx[m], want), (V, path, k, m)
+                        wv = np.full(k, -np.inf, np.float32)
+                        wv[:order.size] = lg[m, order]
+                        assert np.array_equal(vals[m].view(np.uint32), wv.view(np.uint32))
+        finally:
+            ph.close()
