@@ -288,8 +288,6 @@ PrepLayout prep_layout(const archead_handle* h) {
   off = align256(off + sizeof(float) * n_vt * nslot * kTN);
   p.fin_off = off;
   off = align256(off + sizeof(float) * n_vt * kTN);
-  p.wbf_off = off;
-  off = align256(off + sizeof(uint16_t) * size_t(d.r_c + d.r_r) * size_t(d.d));
   p.uc_off = off;
   off = align256(off + size_t(d.V) * nch * 32);   // [c|c] x 16
   p.total = off;
@@ -390,10 +388,8 @@ WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path 
     const size_t ngrp = size_t(d.d / d.g);
     const size_t nch = size_t(exp_chunks(d.r_c) + exp_chunks(d.r_r));
     const size_t n_mt = size_t((M + kTM - 1) / kTM);
-    w.ts_off = off;
-    off = align256(off + sizeof(uint16_t) * size_t(M) * nch * 64);   // [hi|mid|lo|0] x 16
     w.xs_off = off;
-    off = align256(off + sizeof(uint16_t) * size_t(M) * size_t(d.d));
+    off = align256(off + sizeof(uint16_t) * size_t(M) * (size_t(d.d) + nch * 64));
     w.re_off = off;
     off = align256(off + sizeof(float) * n_mt * kTM);
     w.gs_off = off;
@@ -403,7 +399,6 @@ WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path 
     const PrepLayout pl = prep_layout(h);
     w.rat_off = off + pl.rat_off;
     w.fin_off = off + pl.fin_off;
-    w.wbf_off = off + pl.wbf_off;
     w.uc_off = off + pl.uc_off;
     off += pl.total;
     w.ksplit = s1_ksplit(h, call_M ? call_M : M);
@@ -506,10 +501,7 @@ archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
   p.n_vt = (d.V + kTN - 1) / kTN;
   p.ratio = reinterpret_cast<float*>(base + pl.rat_off);
   p.fin = reinterpret_cast<float*>(base + pl.fin_off);
-  p.cv = static_cast<const int8_t*>(h->ptrs.core_v);
-  p.cb = static_cast<const int8_t*>(h->ptrs.corr_b);
   p.rc = int(d.r_c); p.rr = int(d.r_r); p.d = int(d.d);
-  p.wbf = reinterpret_cast<uint16_t*>(base + pl.wbf_off);
   p.cu = static_cast<const int8_t*>(h->ptrs.core_u);
   p.ca = static_cast<const int8_t*>(h->ptrs.corr_a);
   p.urow = nch * 32;
@@ -517,7 +509,7 @@ archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
   p.cu_row = int(core_u_row_bytes(d));
   p.u5 = d.core_u_dtype == ARCHEAD_I5;
   p.ucodes = reinterpret_cast<int8_t*>(base + pl.uc_off);
-  const int64_t work = std::max({p.n_vt * kTN, int64_t(R) * d.d / 8, d.V * (p.urow / 16)});
+  const int64_t work = std::max<int64_t>(p.n_vt * kTN, d.V * (p.urow / 16));
   const int64_t pblocks =
       std::max<int64_t>(1, std::min<int64_t>((work + kBlock - 1) / kBlock, 4 * int64_t(h->n_cu)));
   void* args[] = {&p};
@@ -536,25 +528,26 @@ archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int6
   // 256 rows of x span less than 2 GiB
   if (int64_t(kTM) * ldx * 2 >= (int64_t(1) << 31) && !even)
     return fail(ARCHEAD_E_UNSUPPORTED, "ldx too large for the many-token kernel");
-  char* pb = prep_base(h, w, ws);
   if (!h->prep.load(std::memory_order_acquire)) {
-    archead_status st = launch_prep(h, pb, s);
+    archead_status st = launch_prep(h, prep_base(h, w, ws), s);
     if (st != ARCHEAD_OK) return st;
   }
   Stage1MArgs a;
   a.x = static_cast<const uint16_t*>(x);
   a.ldx = ldx; a.M = M; a.d = int(d.d); a.g = int(d.g);
-  a.wbf = reinterpret_cast<const uint16_t*>(pb + prep_layout(h).wbf_off);
+  a.cv = static_cast<const int8_t*>(h->ptrs.core_v);
+  a.cb = static_cast<const int8_t*>(h->ptrs.corr_b);
   a.sv = static_cast<const uint16_t*>(h->ptrs.core_v_scale);
   a.gv = int(d.r_c ? d.g_v : d.d); a.rc = int(d.r_c);
   a.sb = static_cast<const uint16_t*>(h->ptrs.corr_b_scale);
   a.gb = int(d.r_r ? d.g_b : d.d); a.rr = int(d.r_r);
-  a.tsplit = reinterpret_cast<uint16_t*>(ws + w.ts_off);
+  a.tsplit = reinterpret_cast<uint16_t*>(ws + w.xs_off) + d.d;
   a.nch_u = exp_chunks(d.r_c);
   a.nch = a.nch_u + exp_chunks(d.r_r);
   a.gbias = reinterpret_cast<float*>(ws + w.gb_off);
   a.gsum = reinterpret_cast<float*>(ws + w.gs_off);
   a.xs = reinterpret_cast<uint16_t*>(ws + w.xs_off);
+  a.ldxs = int(d.d) + 64 * a.nch;
   a.rowexp = reinterpret_cast<float*>(ws + w.re_off);
   a.even = even;
   a.ksplit = w.ksplit;
@@ -815,8 +808,8 @@ MfmaArgs mfma_args(const archead_handle* h, int64_t M, const WsLayout& w, char* 
   memset(&a, 0, sizeof a);
   a.codes = static_cast<const uint8_t*>(h->ptrs.res_codes);
   a.x = reinterpret_cast<const uint16_t*>(ws + w.xs_off);
-  a.ldx = d.d;
-  a.tsplit = reinterpret_cast<const uint16_t*>(ws + w.ts_off);
+  a.ldx = d.d + 64 * (exp_chunks(d.r_c) + exp_chunks(d.r_r));
+  a.tsplit = a.x + d.d;
   const PrepLayout pl = prep_layout(h);
   const char* pb = prep_base(h, w, ws);
   a.ucodes = reinterpret_cast<const int8_t*>(pb + pl.uc_off);
@@ -965,7 +958,7 @@ size_t noalloc_bytes(const archead_handle* h, int64_t M) {
   const size_t n_mt = size_t((M + kTM - 1) / kTM);
   const int ks = s1_ksplit(h, M);
   return align256(sizeof(uint16_t) * size_t(M) * nch * 64) + align256(sizeof(float) * n_mt * nslot * kTM) +
-         prep_layout(h).total +
+         prep_layout(h).total + align256(sizeof(uint16_t) * size_t(d.r_c + d.r_r) * size_t(d.d)) +
          (ks > 1 ? align256(sizeof(float) * size_t(ks) * size_t(M) * size_t(d.r_c + d.r_r)) : 0);
 }
 

@@ -48,7 +48,7 @@ struct MfmaArgs {
   const uint8_t* codes;
   const uint16_t* x;       // [M][ldx] bf16, scaled (Stage1MArgs::xs)
   int64_t ldx;
-  const uint16_t* tsplit;  // [M][nch][4][16] bf16: t hi, mid, lo, 0 per 16 rank dimensions
+  const uint16_t* tsplit;  // [M] rows of ldx: [nch][4][16] bf16, t hi, mid, lo, 0 per 16 rank dimensions
   const int8_t* ucodes;    // [V][nch][2][16] int8: U_c then A_w codes (each padded), twice
   const float* gbias;      // [n_mt][d / g][kTM] slot biases of the residual groups
   const float* rowexp;     // [n_mt][kTM] 2^e of each token
@@ -133,7 +133,7 @@ void k_mfma(MfmaArgs a) {
   const int ngrp = a.d / a.g;
   const uint32_t rowbytes = uint32_t(a.d) / 2;
   const uint32_t ldx2 = uint32_t(a.ldx) * 2;
-  const uint32_t trow = uint32_t(a.nch) * 128, urow = uint32_t(a.nch) * 32;
+  const uint32_t urow = uint32_t(a.nch) * 32;
 
   // buffer resources over exactly the bytes this tile may touch (loads past
   // them return zero instead of reading other memory)
@@ -144,8 +144,8 @@ void k_mfma(MfmaArgs a) {
       const_cast<uint8_t*>(a.codes + v0 * int64_t(rowbytes)), 0, int(uint32_t(cols) * rowbytes),
       kBufferWord3);
   const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(a.tsplit + m0 * int64_t(a.nch) * 64), 0, int(uint32_t(rows) * trow),
-      kBufferWord3);
+      const_cast<uint16_t*>(a.tsplit + m0 * a.ldx), 0,
+      int(uint32_t(rows - 1) * ldx2 + uint32_t(a.nch) * 128), kBufferWord3);
   const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<int8_t*>(a.ucodes + v0 * int64_t(urow)), 0, int(uint32_t(cols) * urow),
       kBufferWord3);
@@ -201,7 +201,7 @@ void k_mfma(MfmaArgs a) {
     if (part < G::NX) {
       lds_u8* dst = base + (wid * G::NX + part) * 1024;
       if (res) dma16(rx, dst, xo[part] + uint32_t(s) * (kKS * 2));
-      else dma16(rt, dst, xunit(part, trow) + uint32_t(s - nst) * 128);
+      else dma16(rt, dst, xo[part] + uint32_t(s - nst) * 128);
     } else if (part < G::NX + G::NC) {
       const int ci = part - G::NX;
       lds_u8* dst = base + G::XBYTES + (wid * G::NC + ci) * 1024;
@@ -708,8 +708,7 @@ void k_mfma(MfmaArgs a) {
 // s'_{k-1} / s'_k (0 for k = 0) and fin[vt][c] = s' of the last slot times
 // 2^-(kXExp + kCodeExp), where s' is the fp16 scale with zero replaced by
 // kZeroScale; columns past V repeat row V-1;
-// (b) the factor codes of V_c and B_w as bf16 (exact), wbf[k][i] for the
-// R = r_c + r_r rows; (c) the codes of U_c and A_w side by side per vocabulary
+// (b) the codes of U_c and A_w side by side per vocabulary
 // row, each part zero-padded to a multiple of 16 dimensions, each block of 16
 // stored twice.
 struct PrepArgs {
@@ -722,10 +721,7 @@ struct PrepArgs {
   int64_t n_vt;
   float* ratio;
   float* fin;
-  const int8_t* cv;
-  const int8_t* cb;
   int rc, rr, d;
-  uint16_t* wbf;
   const int8_t* cu;
   const int8_t* ca;
   int urow, rc_pad;      // bytes per ucodes row; padded dimensions of the U part
@@ -759,18 +755,20 @@ struct Stage1MArgs {
   const uint16_t* x;
   int64_t ldx, M;
   int d, g;
-  const uint16_t* wbf;     // [R][d] bf16 factor codes
+  const int8_t* cv;        // [rc][d] V_c codes
+  const int8_t* cb;        // [rr][d] B_w codes
   const uint16_t* sv;
   int gv, rc;
   const uint16_t* sb;
   int gb, rr;
-  uint16_t* tsplit;        // [M][nch][4][16] (hi, mid, lo, 0)
+  uint16_t* tsplit;        // [M] rows of ldxs: [nch][4][16] (hi, mid, lo, 0)
   int nch, nch_u;
   float* gbias;            // [n_mt][d / g][kTM]
   float* gsum;             // [d / g][M] sums of x over the residual groups
   int ksplit;              // workgroups along d
   float* tpart;            // [ksplit][M][R]
-  uint16_t* xs;            // [M][d] scaled x
+  uint16_t* xs;            // [M][ldxs] scaled x, followed in each row by t's parts
+  int ldxs;
   float* rowexp;           // [n_mt][kTM] 2^e
   int even;
   int mblocks, rblocks;    // stage-1 workgroups: mblocks * rblocks * ksplit, then M for xs

@@ -87,14 +87,12 @@ enum class Path { kDec, kMid, kGemv, kTiled };
 struct WsLayout {
   size_t tst_off = 0;    // u64 [M, r_c + r_r] stamped t (decode and several-token kernels)
   // many-token (MFMA) path only:
-  size_t ts_off = 0;     // bf16 [M][blocks][4][16] t split into hi, mid, lo (and 0)
-  size_t xs_off = 0;     // bf16 [M][d] scaled x
+  size_t xs_off = 0;     // bf16 [M][ldxs]: scaled x [d], then [blocks][4][16] t split into hi, mid, lo (and 0)
   size_t re_off = 0;     // fp32 [n_mt][256] the tokens' powers of two
   size_t gs_off = 0;     // fp32 [d / g][M] sums of x over the residual groups
   size_t gb_off = 0;     // fp32 [n_mt][d / g][256] slot biases
   size_t rat_off = 0;    // fp32 [n_vt][slots][256] scale ratios
   size_t fin_off = 0;    // fp32 [n_vt][256] final scales
-  size_t wbf_off = 0;    // bf16 [r_c + r_r][d] factor codes of V_c and B_w
   size_t uc_off = 0;     // int8 [V][blocks][2][16] codes of U_c and A_w, padded, twice
   int ksplit = 1;        // workgroups along d of stage 1
   size_t s1p_off = 0;    // fp32 [ksplit][M][r_c + r_r] stage-1 partials
@@ -129,7 +127,7 @@ WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path 
 // offsets from the start of their block, in the workspace or in a prepared
 // buffer (the same layout in both).
 struct PrepLayout {
-  size_t rat_off = 0, fin_off = 0, wbf_off = 0, uc_off = 0, total = 0;
+  size_t rat_off = 0, fin_off = 0, uc_off = 0, total = 0;
 };
 PrepLayout prep_layout(const archead_handle* h);
 bool use_gemv(const archead_handle* h, int64_t M);

@@ -42,23 +42,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
     }
     a.fin[vt * kTN + c] = prev * ldexpf(1.f, -(kXExp + kCodeExp));
   }
-  // (b) 8 codes per thread
-  const int64_t n8 = int64_t(a.rc + a.rr) * a.d / 8;
-  for (int64_t e = t0; e < n8; e += nthr) {
-    const int64_t k = e * 8 / a.d, i = e * 8 % a.d;
-    const int8_t* src = k < a.rc ? a.cv + k * a.d + i : a.cb + (k - a.rc) * a.d + i;
-    const uint2 w = *reinterpret_cast<const uint2*>(src);
-    uint32_t o[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t wj = j < 2 ? w.x : w.y;
-      const int sh = 16 * (j & 1);
-      const float lo = float(int8_t(wj >> sh)), hi = float(int8_t(wj >> (sh + 8)));
-      o[j] = (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
-    }
-    *reinterpret_cast<uint4*>(a.wbf + e * 8) = make_uint4(o[0], o[1], o[2], o[3]);
-  }
-  // (c) 16 bytes per thread (row-major, so lanes write consecutive chunks)
+  // (b) 16 bytes per thread (row-major, so lanes write consecutive chunks)
   const int64_t n16 = a.V * (a.urow / 16);
   for (int64_t e = t0; e < n16; e += nthr) {
     const int64_t v = e / (a.urow / 16);
@@ -106,7 +90,7 @@ __device__ __forceinline__ void scale_row(const Stage1MArgs& a, int64_t m, int* 
       const uint32_t hi = __float_as_uint(ldexpf(bf16_hi(v[j]), k));
       v[j] = (lo >> 16) | (hi & 0xffff0000u);
     }
-    *reinterpret_cast<u32x4_t*>(a.xs + m * a.d + i) = v;
+    *reinterpret_cast<u32x4_t*>(a.xs + m * a.ldxs + i) = v;
   }
   if (threadIdx.x == 0) a.rowexp[m] = ldexpf(1.f, e);
 }
@@ -138,15 +122,15 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
   const int nblk = R - kb >= kS1MCols ? NB : (R - kb + 15) / 16;
 
   // this lane's factor row in each 16-column block (clamped; masked on store)
-  const uint16_t* wrow[NB];
+  const int8_t* wrow[NB];
   const uint16_t* srow[NB];
   int sgrp[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     int k = kb + 16 * nb + lr;
     k = k < R ? k : (R > 0 ? R - 1 : 0);
-    wrow[nb] = a.wbf + int64_t(k) * a.d + 8 * q;
     const bool core = k < a.rc;
+    wrow[nb] = (core ? a.cv + int64_t(k) * a.d : a.cb + int64_t(k - a.rc) * a.d) + 8 * q;
     sgrp[nb] = core ? a.gv : a.gb;
     srow[nb] = core ? a.sv + int64_t(k) * (a.d / a.gv) : a.sb + int64_t(k - a.rc) * (a.d / a.gb);
   }
@@ -156,15 +140,16 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  bf16x8_t A, An, B[NB], Bn[NB];
+  bf16x8_t A, An;
+  u32x2_t B[NB], Bn[NB];   // int8 codes
   float s[NB], sn[NB];
-  auto load = [&](int c, bf16x8_t& A_, bf16x8_t* B_, float* s_) {
+  auto load = [&](int c, bf16x8_t& A_, u32x2_t* B_, float* s_) {
     const int k0 = 32 * c;
     A_ = *reinterpret_cast<const bf16x8_t*>(xrow + k0);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       if (nb < nblk) {
-        B_[nb] = *reinterpret_cast<const bf16x8_t*>(wrow[nb] + k0);
+        B_[nb] = *reinterpret_cast<const u32x2_t*>(wrow[nb] + k0);
         s_[nb] = f16_to_f32(srow[nb][k0 / sgrp[nb]]);
       }
     }
@@ -177,7 +162,7 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
     for (int nb = 0; nb < NB; ++nb) {
       if (nb < nblk) {
         const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
-        acc[nb] += s[nb] * __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[nb], z, 0, 0, 0);
+        acc[nb] += s[nb] * __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, int8x8_to_bf16(B[nb].x, B[nb].y), z, 0, 0, 0);
       }
     }
     if (do_sum && (c + 1) % cpg == 0) {
@@ -235,7 +220,7 @@ __global__ __launch_bounds__(kBlock) void k_stage1m_fin(Stage1MArgs a) {
       md = (__bf16)r1;
       lo = (__bf16)(r1 - float(md));
     }
-    uint16_t* dst = a.tsplit + (m * a.nch + c) * 64 + i;
+    uint16_t* dst = a.tsplit + m * a.ldxs + c * 64 + i;
     dst[0] = __builtin_bit_cast(uint16_t, hi);
     dst[16] = __builtin_bit_cast(uint16_t, md);
     dst[32] = __builtin_bit_cast(uint16_t, lo);
