@@ -409,9 +409,10 @@ constexpr int kExpDims = 16;                 // rank dimensions per expansion st
 // workgroup: NW = 8 (2 x 4 waves of TM/2 x 64; one workgroup per CU) or
 // NW = 4 (1 x 4 waves of TM x 64; TM = 128: two workgroups per CU, TM = 64:
 // three), whose stage barriers are independent, so one's LDS waits, tile
-// start and epilogue overlap the others' MFMAs.  A stage holds x [TM][kKS] bf16,
-// codes [kTN][kKS/2] and, in a stage that starts a scale slot, the scale
-// ratios of the kTN columns and the slot biases of the TM rows.
+// start and epilogue overlap the others' MFMAs.  A stage holds x [TM][kKS] bf16
+// and, where it starts a scale slot, the scale ratios of the kTN columns and
+// the slot biases of the TM rows; the codes of two stages, [kTN][kKS], have one
+// place of their own.
 template <int TM, int NW = kMWaves>
 struct MGeomT {
   static constexpr int WMW = NW / 4;                  // waves along the tokens
@@ -419,15 +420,15 @@ struct MGeomT {
   static constexpr int WN = kTN / (NW / WMW);         // vocabulary rows per wave
   static constexpr int MI = WM / 32, NI = WN / 32;    // 32 x 32 MFMA blocks per wave
   static constexpr int XBYTES = TM * kKS * 2;         // x [TM][kKS] bf16
-  static constexpr int CBYTES = kTN * kKS / 2;        // codes [kTN][kKS/2]
-  static constexpr int RAT = XBYTES + CBYTES;         // fp32 [kTN] scale ratios
+  static constexpr int CBYTES = 2 * kTN * kKS / 2;    // codes of two stages [kTN][kKS]
+  static constexpr int RAT = XBYTES;                  // fp32 [kTN] scale ratios
   static constexpr int BIAS = RAT + kTN * 4;          // fp32 [TM] slot biases
   static constexpr int STAGE = BIAS + TM * 4;
   static constexpr int NX = XBYTES / 1024 / NW;       // x loads per wave and stage
-  static constexpr int NC = CBYTES / 1024 / NW;       // code loads per wave and stage
-  static constexpr int NLD = NX + NC;                 // of them in every stage
-  static constexpr int NL = NLD + 2;                  // loads per wave and stage (ratios, biases)
-  static constexpr int LDS = kRing * STAGE;
+  static constexpr int NC = CBYTES / 1024 / NW;       // code loads per wave and two stages
+  static constexpr int NLX = NX + 2;                  // the other loads per wave and stage (ratios, biases)
+  static constexpr int CODES = kRing * STAGE;         // the codes follow the ring
+  static constexpr int LDS = CODES + CBYTES;
   static constexpr int WGS = NW == 8 ? 1 : (TM == 128 ? 2 : 3);   // workgroups per CU
   static_assert(NW == 8 || (NW == 4 && (TM == 128 || TM == 64)), "layouts built");
   static_assert(XBYTES % (1024 * NW) == 0 && CBYTES % (1024 * NW) == 0, "whole loads");
@@ -439,7 +440,7 @@ using MGeom = MGeomT<kTM>;
 // 16-byte unit swizzles; only the low four bits of the row matter, so every
 // lane's swizzle is fixed for all its fragments
 __device__ __forceinline__ int swz_x(int r) { return ((r & 15) ^ ((r & 15) >> 3)) & 7; }
-__device__ __forceinline__ int swz_c(int c) { return (c >> 2) & 1; }
+__device__ __forceinline__ int swz_c(int c) { return (c >> 1) & 3; }
 
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, lds_u8* dst, uint32_t voff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -450,12 +451,13 @@ __device__ __forceinline__ void dma4(__amdgpu_buffer_rsrc_t r, lds_u8* dst, uint
       r, reinterpret_cast<__attribute__((address_space(3))) void*>(dst), 4, voff, 0, 0, 0);
 }
 
-// Wait until at most N of this wave's vector-memory loads are in flight, then
-// meet the other waves.  The memory clobber keeps LDS accesses on their side
-// of it.
+// Wait until at most N of this wave's vector-memory loads are in flight and
+// its LDS reads are done (the loads issued after the meeting overwrite what
+// they read), then meet the other waves.  The memory clobber keeps LDS
+// accesses on their side of it.
 template <int N>
 __device__ __forceinline__ void wait_loads_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
 template <typename T>

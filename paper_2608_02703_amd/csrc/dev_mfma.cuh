@@ -172,7 +172,7 @@ void k_mfma(MfmaArgs a) {
   };
   auto cunit = [&](int ci, uint32_t stride) {
     const int off = (wid * G::NC + ci) * 1024 + 16 * lane;
-    const int c = off / (kKS / 2), p = (off % (kKS / 2)) / 16;
+    const int c = off / kKS, p = (off % kKS) / 16;
     return uint32_t(c < cols ? c : cols - 1) * stride + 16u * uint32_t(p ^ swz_c(c));
   };
   uint32_t xo[G::NX];
@@ -184,16 +184,18 @@ void k_mfma(MfmaArgs a) {
   const uint32_t ao_bias = uint32_t(wid * 64 + lane) * 4;
   const uint32_t ao_rat = uint32_t((wid & 3) * 64 + lane) * 4;
 
-  const int nst = a.d / kKS, spg = a.g / kKS, ntot = nst + a.nch;
+  // residual stages (an odd count is followed by one that computes nothing,
+  // as the codes come for two stages), then the expansion's
+  const int nres = a.d / kKS, nst = (nres + 1) & ~1, spg = a.g / kKS, ntot = nst + a.nch;
   const int st_a = nst + a.nch_u;   // first stage of the A_w part
   const int slot_a = ngrp + (a.nch_u > 0 ? 1 : 0);
   auto slot_of = [&](int s) { return s < nst ? s / spg : (s < st_a ? ngrp : slot_a); };
-  auto slot_start = [&](int s) { return s < nst ? s % spg == 0 : (s == nst || s == st_a); };
+  auto slot_start = [&](int s) { return s < nst ? s < nres && s % spg == 0 : (s == nst || s == st_a); };
   int sg_ahead = 2 % spg, slot_ahead = 2 / spg;   // of stage s + 2 in the residual loop
-  // load PART (0 .. NL-1) of this wave's share of stage s into ring slot
-  // buf: x (or t) units, code units, then, where the stage starts a
-  // slot, 64 scale ratios and (residual groups) 64 slot biases.  KIND: 1
-  // a residual stage, 2 an expansion stage, 3 either (checked).
+  // load PART (0 .. NLX-1) of this wave's share of stage s, apart from its
+  // codes, into ring slot buf: x (or t) units, then, where the stage starts a
+  // slot, 64 scale ratios and (residual groups) 64 slot biases.  KIND: 1 a
+  // residual stage, 2 an expansion stage, 3 either (checked).
   auto issue_part = [&](int s, int buf, int part, auto kind) {
     constexpr int KIND = decltype(kind)::value;
     lds_u8* base = L + buf * G::STAGE;
@@ -202,24 +204,25 @@ void k_mfma(MfmaArgs a) {
       lds_u8* dst = base + (wid * G::NX + part) * 1024;
       if (res) dma16(rx, dst, xo[part] + uint32_t(s) * (kKS * 2));
       else dma16(rt, dst, xo[part] + uint32_t(s - nst) * 128);
-    } else if (part < G::NX + G::NC) {
-      const int ci = part - G::NX;
-      lds_u8* dst = base + G::XBYTES + (wid * G::NC + ci) * 1024;
-      if (res) dma16(rc, dst, co[ci] + uint32_t(s) * (kKS / 2));
-      else dma16(ru, dst, cunit(ci, urow) + uint32_t(s - nst) * 32);
     } else if (KIND == 1 ? sg_ahead == 0 : slot_start(s)) {
       const uint32_t k = uint32_t(KIND == 1 ? slot_ahead : slot_of(s)) * 1024u;
-      if (part == G::NLD) dma4(rrat, base + G::RAT + (wid & 3) * 256, ao_rat + k);
+      if (part == G::NX) dma4(rrat, base + G::RAT + (wid & 3) * 256, ao_rat + k);
       else if (wid < TM / 64 && res) dma4(rbias, base + G::BIAS + wid * 256, ao_bias + k);
     }
   };
+  // load CI (0 .. NC-1) of this wave's share of the codes of stages s, s + 1:
+  // 64 bytes of a row (32-byte pieces, one stage's, stream the head 15% slower)
+  auto issue_code = [&](int s, int ci, auto kind) {
+    constexpr int KIND = decltype(kind)::value;
+    lds_u8* dst = L + G::CODES + (wid * G::NC + ci) * 1024;
+    if (KIND == 1 || (KIND == 3 && s < nst)) dma16(rc, dst, co[ci] + uint32_t(s) * (kKS / 2));
+    else dma16(ru, dst, cunit(ci, urow) + uint32_t(s - nst) * 32);
+  };
   using kMain = std::integral_constant<int, 1>;
-  using kExp = std::integral_constant<int, 2>;
   using kAny = std::integral_constant<int, 3>;
-  using kNone = std::integral_constant<int, 0>;
   auto issue = [&](int s, int buf) {
 #pragma unroll
-    for (int part = 0; part < G::NL; ++part) issue_part(s, buf, part, kAny{});
+    for (int part = 0; part < G::NLX; ++part) issue_part(s, buf, part, kAny{});
   };
 
   // Fragment offsets within a stage.  Residual stages: half-wave h holds code
@@ -231,8 +234,9 @@ void k_mfma(MfmaArgs a) {
   uint32_t aoff[kSteps];
 #pragma unroll
   for (int t = 0; t < kSteps; ++t) aoff[t] = arow + 16u * (uint32_t(4 * h + t) ^ sx);
-  const uint32_t boff =
-      G::XBYTES + uint32_t(G::WN * wn + lr) * 32 + 16u * uint32_t(h ^ swz_c(lr));
+  // codes of stage parity b: unit 2 b + h of the row's four
+  const uint32_t brow = G::CODES + uint32_t(G::WN * wn + lr) * kKS;
+  const uint32_t boff[2] = {brow + 16u * uint32_t(h ^ swz_c(lr)), brow + 16u * uint32_t((2 + h) ^ swz_c(lr))};
 
   f32x16_t acc[MI][NI];
 #pragma unroll
@@ -274,6 +278,8 @@ void k_mfma(MfmaArgs a) {
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) rf[mi] = a.rowexp[m0 + WM * wm + 32 * mi + lr];
   issue(0, 0);
+#pragma unroll
+  for (int ci = 0; ci < G::NC; ++ci) issue_code(0, ci, kAny{});
   if (ntot > 1) issue(1, 1);
 
   // slot start: rescale to the slot's scale and (residual groups) add its bias
@@ -300,59 +306,67 @@ void k_mfma(MfmaArgs a) {
   // Stage s computes K-steps 0 .. 3.  Half way through it waits for its own
   // share of stage s + 1 and meets the other waves: stage s + 1 is then in
   // LDS, and every wave is past stage s - 1, whose ring slot takes the loads
-  // of stage s + 2 (issued one at a time between the MFMAs that follow).
-  // The last K-step reads the next stage's first fragments, so no wave
-  // starts a stage waiting for LDS.
+  // of stage s + 2 (issued one at a time between the MFMAs that follow); where
+  // s is even, so are the codes of stages s + 2, s + 3, in the place of those
+  // of s, s + 1, which every wave has in registers by then.  The last K-step
+  // reads the next stage's first fragments (and the next two stages' codes),
+  // so no wave starts a stage waiting for LDS.
   bf16x8_t A[MI];
-  u32x4_t braw[NI];
+  u32x4_t braw[NI][2];
   const lds_u8* base = L;            // ring slot of the stage being computed
   int nslot_ring = 2 % kRing;        // ring slot of stage s + 2
   auto ring_next = [&](const lds_u8* p) {
     return p == L + (kRing - 1) * G::STAGE ? (const lds_u8*)L : p + G::STAGE;
   };
-  auto load_first = [&](const lds_u8* p) {
+  auto load_codes = [&] {
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) braw[ni] = lds_load<u32x4_t>(p + boff + ni * 32 * (kKS / 2));
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) braw[ni][b] = lds_load<u32x4_t>(L + boff[b] + ni * 32 * kKS);
+  };
+  auto load_first = [&](const lds_u8* p) {
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) A[mi] = lds_load<bf16x8_t>(p + aoff[0] + mi * 64 * kKS);
   };
-  if (ntot > 1) wait_loads_barrier<G::NLD>();   // stage 1 has at least NLD loads in flight
+  if (ntot > 1) wait_loads_barrier<G::NX>();   // stage 1 has at least NX loads in flight
   else wait_loads_barrier<0>();
+  load_codes();
   load_first(base);
   if constexpr (XE == 1) {
 #pragma unroll
     for (int t = 0; t < kSteps; ++t) load_dense(0, t);
   }
 
-  // ISSUE says how the loads of stage s + 2 are issued: 0 none, 1 residual
-  // source, 2 expansion source, 3 either (checked).
+  // issue_kind: kMain where stage s + 2 is a residual stage, else kAny (checked)
   int sg = 0;   // stage index within its scale group
   constexpr int kHalfMfma = (kSteps - kSteps / 2) * MI * NI;   // MFMA tiles after the barrier
-  constexpr int kPer = kHalfMfma / G::NL > 0 ? kHalfMfma / G::NL : 1;   // tiles between two loads
-  constexpr int kBatch = (G::NL + kHalfMfma - 1) / kHalfMfma;           // loads at a time
-  auto issue_after = [&](int s, int tile, auto issue_kind) {
+  // loads of an even / odd stage issued after tile `tile` of them
+  auto issue_after = [&](int s, int tile, auto issue_kind, auto parity) {
     constexpr int ISSUE = decltype(issue_kind)::value;
+    constexpr int NCODE = decltype(parity)::value == 0 ? G::NC : 0, N = G::NLX + NCODE;
+    constexpr int kPer = kHalfMfma / N > 0 ? kHalfMfma / N : 1;   // tiles between two loads
+    constexpr int kBatch = (N + kHalfMfma - 1) / kHalfMfma;       // loads at a time
     if (tile % kPer) return;
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
-      const int part = tile / kPer * kBatch + k;
-      if (part < G::NL) {
-        if constexpr (ISSUE == 1) issue_part(s + 2, nslot_ring, part, kMain{});
-        if constexpr (ISSUE == 2) issue_part(s + 2, nslot_ring, part, kExp{});
-        if constexpr (ISSUE == 3) if (s + 2 < ntot) issue_part(s + 2, nslot_ring, part, kAny{});
-      }
+      const int part = tile / kPer * kBatch + k;   // the codes first: they come from furthest
+      if (part >= N) continue;
+      auto one = [&](auto kind) {
+        if (part < NCODE) issue_code(s + 2, part, kind);
+        else issue_part(s + 2, nslot_ring, part - NCODE, kind);
+      };
+      if constexpr (ISSUE == 1) one(kMain{});
+      if constexpr (ISSUE == 3) if (s + 2 < ntot) one(kAny{});
     }
   };
   auto ring_step = [&] {
     base = ring_next(base);
     nslot_ring = nslot_ring == kRing - 1 ? 0 : nslot_ring + 1;
   };
-  auto main_stage = [&](int s, auto issue_kind) {
+  auto main_stage = [&](int s, auto issue_kind, auto parity) {
+    constexpr int PAR = decltype(parity)::value;
     const lds_u8* nbase = ring_next(base);
     if (sg == 0) rescale(base, std::true_type{});
-    u32x4_t bcur[NI];
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) bcur[ni] = braw[ni];
 #pragma unroll
     for (int t = 0; t < kSteps; ++t) {
       // (the fidelity pass has issued NI dense loads in each K-step so far,
@@ -360,14 +374,12 @@ void k_mfma(MfmaArgs a) {
       if (t == kSteps / 2) wait_loads_barrier<XE == 1 ? kSteps / 2 * NI : 0>();
       bf16x8_t B[NI];
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni) B[ni] = unpack8_sub<XE != 0>(bcur[ni][t]);
+      for (int ni = 0; ni < NI; ++ni) B[ni] = unpack8_sub<XE != 0>(braw[ni][PAR][t]);
       bf16x8_t An[MI];
       if (t + 1 < kSteps) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) An[mi] = lds_load<bf16x8_t>(base + aoff[t + 1] + mi * 64 * kKS);
       } else {
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) braw[ni] = lds_load<u32x4_t>(nbase + boff + ni * 32 * (kKS / 2));
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) An[mi] = lds_load<bf16x8_t>(nbase + aoff[0] + mi * 64 * kKS);
       }
@@ -378,9 +390,11 @@ void k_mfma(MfmaArgs a) {
           acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B[ni], A[mi], acc[mi][ni], 0, 0, 0);
           if constexpr (XE == 1)
             accd[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dfr[ni][t], A[mi], accd[mi][ni], 0, 0, 0);
-          if (t >= kSteps / 2) issue_after(s, ((t - kSteps / 2) * MI + mi) * NI + ni, issue_kind);
+          if (t >= kSteps / 2) issue_after(s, ((t - kSteps / 2) * MI + mi) * NI + ni, issue_kind, parity);
         }
-      load_dense(s + 1 < nst ? s + 1 : s, t);
+      // (B holds this K-step's codes; the next stages' take their place)
+      if (PAR == 1 && t == kSteps - 1) load_codes();
+      load_dense(s + 1 < nres ? s + 1 : s, t);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) A[mi] = An[mi];
     }
@@ -391,13 +405,25 @@ void k_mfma(MfmaArgs a) {
     }
     ring_step();
   };
-  auto exp_stage = [&](int s, auto issue_kind) {
+  // the stage after an odd number of residual stages: only its share of the
+  // loads, and the meeting
+  auto empty_stage = [&](int s) {
+    wait_loads_barrier<0>();
+#pragma unroll
+    for (int part = 0; part < G::NLX; ++part)
+      if (s + 2 < ntot) issue_part(s + 2, nslot_ring, part, kAny{});
+    load_codes();
+    ring_step();
+  };
+  auto exp_stage = [&](int s, auto issue_kind, auto parity) {
+    constexpr int PAR = decltype(parity)::value;
     if (s == nst || s == st_a) rescale(base, std::false_type{});
     bf16x8_t B[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
-      const u32x2_t c = lds_load<u32x2_t>(base + boff + 8 * h + ni * 32 * (kKS / 2));
-      B[ni] = int8x8_to_bf16(c.x, c.y);
+      // half h takes the copy in unit 2 PAR + h, dimensions 8 h .. 8 h + 7
+      const u32x4_t c = braw[ni][PAR];
+      B[ni] = int8x8_to_bf16(h ? c[2] : c[0], h ? c[3] : c[1]);
     }
 #pragma unroll
     for (int t = 0; t < kExpParts; ++t) {
@@ -410,21 +436,32 @@ void k_mfma(MfmaArgs a) {
         for (int ni = 0; ni < NI; ++ni) {
           acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B[ni], Ae, acc[mi][ni], 0, 0, 0);
           if (t >= kExpParts - 2)
-            issue_after(s, ((t - kExpParts + 2) * MI + mi) * NI + ni, issue_kind);
+            issue_after(s, ((t - kExpParts + 2) * MI + mi) * NI + ni, issue_kind, parity);
         }
       }
     }
+    if (PAR == 1) load_codes();
     ring_step();
   };
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
   int s = 0;
 #pragma unroll 1
-  for (; s + 2 < nst; ++s) main_stage(s, kMain{});
+  for (; s + 3 < nres; s += 2) {
+    main_stage(s, kMain{}, Even{});
+    main_stage(s + 1, kMain{}, Odd{});
+  }
 #pragma unroll 1
-  for (; s < nst; ++s) main_stage(s, kAny{});
+  for (; s < nst; s += 2) {
+    main_stage(s, kAny{}, Even{});
+    if (s + 1 < nres) main_stage(s + 1, kAny{}, Odd{});
+    else empty_stage(s + 1);
+  }
 #pragma unroll 1
-  for (; s + 2 < ntot; ++s) exp_stage(s, kExp{});
-#pragma unroll 1
-  for (; s < ntot; ++s) exp_stage(s, kNone{});
+  for (; s < ntot; s += 2) {
+    exp_stage(s, kAny{}, Even{});
+    if (s + 1 < ntot) exp_stage(s + 1, kAny{}, Odd{});
+  }
 
   // the last slot's scales and the token's power of two (dense sums: without
   // the scale, and 2^-kXExp apart, as 2^(e - kXExp) may be below fp32's range)
