@@ -779,21 +779,31 @@ archead_status launch_mid(const archead_handle* h, const void* x, int64_t M, int
 int tiled_tm(int64_t M) { return M <= 128 ? 128 : kTM; }
 
 // Tile rows and waves per workgroup of the tiled kernel for a call of M
-// tokens: 64-row tiles of 4 waves, three workgroups per CU, up to
-// kTiled64MaxM tokens; 128-row tiles of 4 waves, two workgroups per CU, up
-// to kTiledNw4MaxM tokens (measured 10-25% faster than one workgroup of 8
-// waves per CU at M = 16 .. 1024, where tile starts, LDS waits and the
-// epilogue would leave the matrix unit idle); above, 256-row tiles of 8
-// waves (equal at M = 4096, where the chip runs at its power limit).
+// tokens: 256-row tiles of 8 waves above kTiledNw4MaxM tokens (equal to 128-row
+// tiles at M = 4096, where the chip runs at its power limit); 64-row tiles of 4
+// waves, three workgroups per CU, up to kTiled64MaxM tokens; between them 128-
+// or 64-row tiles of 4 waves, whichever fills its rounds of resident
+// workgroups (2 or 3 per CU) better: a 64-row round takes about 0.8 of a
+// 128-row one (Qwen head M = 512: 89-100 against 120-130 us), and a last round
+// costs about half of what it leaves idle (V = 50257, d = 1536, M = 333, 1.15
+// against 1.54 rounds: 114 us per call with 128-row tiles, 106 with 64-row
+// ones; Qwen M = 512, 4.6 against 6.2: 603 and 624; Gemma M = 100, 2 against
+// 2.7: 194 and 206).
 // The launch settings ARCHEAD_LAUNCH_TILE_WAVES (4 or 8) and
 // ARCHEAD_LAUNCH_TILE_ROWS (64 or 128, with 4 waves) override the choice.
 constexpr int64_t kTiled64MaxM = 64;
 constexpr int64_t kTiledNw4MaxM = 1024;
 struct TiledShape { int tm, nw; };
+double tile_rounds(const archead_handle* h, int64_t M, int tm, int wgs) {
+  const int64_t n_vt = (h->desc.V + kTN - 1) / kTN;
+  const double r = double(n_vt * ((M + tm - 1) / tm)) / double(h->n_cu * wgs);
+  return 0.5 * (r + ceil(r));
+}
 TiledShape tiled_shape(const archead_handle* h, int64_t M) {
   TiledShape t = M <= kTiled64MaxM    ? TiledShape{64, 4}
                  : M <= kTiledNw4MaxM ? TiledShape{128, 4}
                                       : TiledShape{kTM, 8};
+  if (t.tm == 128 && 0.8 * tile_rounds(h, M, 64, 3) < tile_rounds(h, M, 128, 2)) t.tm = 64;
   const int64_t nw = h->launch[ARCHEAD_LAUNCH_TILE_WAVES].load(std::memory_order_relaxed);
   const int64_t tm = h->launch[ARCHEAD_LAUNCH_TILE_ROWS].load(std::memory_order_relaxed);
   if (nw == 4) t = TiledShape{128, 4};
