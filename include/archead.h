@@ -315,16 +315,16 @@ archead_status archead_logit_fidelity_head(const archead_handle* h, const void* 
  * is archead_logits_argmax's index.  This is the candidate set of top-k
  * decoding and of the top-k agreement metric ("Logit Fidelity", Section 4 and
  * its Table 8: top-1, top-5, top-10).  A single token on the decode GEMV
- * (M = 1 at the default ranges) selects inside the head pass: the [V]
- * logits are never written, each workgroup leaves its k best pairs in the
+ * (M = 1 at the default ranges) with k <= 6 selects inside the head pass: the
+ * [V] logits are never written, each workgroup leaves its k best pairs in the
  * workspace and a merge kernel combines them.  Otherwise the logits of up to
  * 256 tokens at a time go to the workspace in fp32 (about 256 * V * 4
- * bytes) and a selection kernel reads them back.
+ * bytes), and two selection kernels read them back.
  *   k          1 <= k <= min(ARCHEAD_TOPK_MAX, V)
  *   vals       device fp32 [M, ldk], 4-byte aligned, or NULL
  *   idx        device int64 [M, ldk], 8-byte aligned; ldk >= k
  *   ws         archead_workspace_bytes(h, M, ARCHEAD_OP_TOPK) bytes (it
- *              holds lists of ARCHEAD_TOPK_MAX entries, so any k fits)
+ *              fits any k)
  * NaN logits are never selected; slots that fewer than k non-NaN logits
  * leave empty get (-inf, -1).  Other arguments and errors as
  * archead_logits, plus ARCHEAD_E_INVALID_ARG for k out of range or

@@ -316,6 +316,8 @@ bool topk_fused(const archead_handle* h, int64_t M) {
                          gemv_mode(h).gen) != nullptr;
 }
 
+// One token may take either form (by k, which the layout does not know): both
+// have their place.
 static WsLayout topk_layout(const archead_handle* h, int64_t M) {
   WsLayout w;
   const archead_desc& d = h->desc;
@@ -325,35 +327,36 @@ static WsLayout topk_layout(const archead_handle* h, int64_t M) {
     off = w.total;
     w.tk_fused = true;
     w.n_part = gemv_grid(h, 1, false, true);
-  } else {
-    const int64_t chunk = M < kTopKChunk ? M : kTopKChunk;
-    w.tk_chunk = chunk;
-    w.tk_lg_off = 0;
-    off = align256(sizeof(float) * size_t(chunk) * size_t(d.V));
-    w.tk_in_off = off;
-    // every chunk runs on the kernel the whole call would take, so the
-    // logits are those archead_logits gives for the same M
-    w.tk_path = choose_path(h, M);
-    size_t inner = ws_layout_path(h, chunk, ARCHEAD_OP_LOGITS, w.tk_path).total;
-    if (M % chunk) {
-      const size_t t = ws_layout_path(h, M % chunk, ARCHEAD_OP_LOGITS, w.tk_path).total;
-      inner = t > inner ? t : inner;
-    }
-    off = align256(off + inner);
-    int64_t cs = kTopKChunkUnit;
-    while ((d.V + cs - 1) / cs > kTopKChunks) cs *= 2;
-    w.tk_cs = int(cs);
-    w.tk_n_chunk = int((d.V + cs - 1) / cs);
-    w.tk_key_off = off;
-    w.total = align256(off + sizeof(uint32_t) * size_t(chunk) * size_t(w.tk_n_chunk));
-    return w;
+    const size_t lists = size_t(w.n_part) * kTopKMaxK;
+    w.tk_pv_off = off;
+    off = align256(off + sizeof(float) * lists);
+    w.tk_pi_off = off;
+    off = align256(off + sizeof(int32_t) * lists);
   }
-  const size_t lists = size_t(w.n_part) * kTopKMaxK;
-  w.tk_pv_off = off;
-  off = align256(off + sizeof(float) * lists);
-  w.tk_pi_off = off;
-  off = align256(off + sizeof(int32_t) * lists);
-  w.total = off;
+  const int64_t chunk = M < kTopKChunk ? M : kTopKChunk;
+  w.tk_chunk = chunk;
+  w.tk_lg_off = off;
+  off = align256(off + sizeof(float) * size_t(chunk) * size_t(d.V));
+  w.tk_in_off = off;
+  // every chunk runs on the kernel the whole call would take, so the
+  // logits are those archead_logits gives for the same M
+  w.tk_path = choose_path(h, M);
+  size_t inner = ws_layout_path(h, chunk, ARCHEAD_OP_LOGITS, w.tk_path).total;
+  if (M % chunk) {
+    const size_t t = ws_layout_path(h, M % chunk, ARCHEAD_OP_LOGITS, w.tk_path).total;
+    inner = t > inner ? t : inner;
+  }
+  off = align256(off + inner);
+  // chunks of 64 logits while a row has no more than kTopKChunks of them (a
+  // short row then still has more chunks than k), else of 256, 1024, 2048, ...
+  int64_t cs = kTopKChunkUnit;
+  if (d.V > cs * kTopKChunks) cs = 4 * kTopKChunkUnit;
+  if (d.V > cs * kTopKChunks) cs = kTopKWave;
+  while (d.V > cs * kTopKChunks) cs *= 2;
+  w.tk_cs = int(cs);
+  w.tk_n_chunk = int((d.V + cs - 1) / cs);
+  w.tk_key_off = off;
+  w.total = align256(off + sizeof(uint32_t) * size_t(chunk) * size_t(w.tk_n_chunk));
   return w;
 }
 
@@ -484,10 +487,9 @@ char* prep_base(const archead_handle* h, const WsLayout& w, char* ws) {
 // The head-derived tables (tile-major residual scale ratios, final scales,
 // bf16 factor codes of V_c / B_w, paired U_c / A_w codes) into the block at
 // base, laid out as prep_layout says.
-archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
+PrepArgs prep_args(const archead_handle* h, char* base) {
   const archead_desc& d = h->desc;
   const PrepLayout pl = prep_layout(h);
-  const int R = int(d.r_c + d.r_r);
   const int nch_u = exp_chunks(d.r_c), nch = nch_u + exp_chunks(d.r_r);
   PrepArgs p;
   p.rs = static_cast<const uint16_t*>(h->ptrs.res_scales);
@@ -509,11 +511,20 @@ archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
   p.cu_row = int(core_u_row_bytes(d));
   p.u5 = d.core_u_dtype == ARCHEAD_I5;
   p.ucodes = reinterpret_cast<int8_t*>(base + pl.uc_off);
-  const int64_t work = std::max<int64_t>(p.n_vt * kTN, d.V * (p.urow / 16));
-  const int64_t pblocks =
-      std::max<int64_t>(1, std::min<int64_t>((work + kBlock - 1) / kBlock, 4 * int64_t(h->n_cu)));
+  return p;
+}
+
+// Workgroups of `block` threads that build the tables.
+int prep_blocks(const archead_handle* h, const PrepArgs& p, int block) {
+  const int64_t work = std::max<int64_t>(p.n_vt * kTN, p.V * (p.urow / 32));
+  return int(std::max<int64_t>(1, std::min<int64_t>((work + block - 1) / block, 1024 / block * int64_t(h->n_cu))));
+}
+
+archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
+  PrepArgs p = prep_args(h, base);
+  p.blocks = prep_blocks(h, p, kBlock);
   void* args[] = {&p};
-  hipError_t e = hipLaunchKernel(kern::prep(), dim3(unsigned(pblocks)), dim3(kBlock), args, 0, s);
+  hipError_t e = hipLaunchKernel(kern::prep(), dim3(unsigned(p.blocks)), dim3(kBlock), args, 0, s);
   return e == hipSuccess ? ARCHEAD_OK : hip_fail(e, "prologue launch");
 }
 
@@ -528,9 +539,11 @@ archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int6
   // 256 rows of x span less than 2 GiB
   if (int64_t(kTM) * ldx * 2 >= (int64_t(1) << 31) && !even)
     return fail(ARCHEAD_E_UNSUPPORTED, "ldx too large for the many-token kernel");
+  PrepArgs p;
+  memset(&p, 0, sizeof p);
   if (!h->prep.load(std::memory_order_acquire)) {
-    archead_status st = launch_prep(h, prep_base(h, w, ws), s);
-    if (st != ARCHEAD_OK) return st;
+    p = prep_args(h, ws + w.rat_off);
+    p.blocks = prep_blocks(h, p, kS1MBlock);
   }
   Stage1MArgs a;
   a.x = static_cast<const uint16_t*>(x);
@@ -554,13 +567,13 @@ archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int6
   a.tpart = reinterpret_cast<float*>(ws + w.s1p_off);
   const int64_t mblocks = (M + kS1MTok - 1) / kS1MTok;
   const int64_t rblocks = R > 0 ? (R + kS1MCols - 1) / kS1MCols : 1;
-  const int64_t grid = mblocks * rblocks * a.ksplit + M;
+  const int64_t grid = p.blocks + mblocks * rblocks * a.ksplit + M;
   const int64_t mpad = (M + kTM - 1) / kTM * kTM;
   const int64_t fgrid = (M * a.nch * kExpDims + mpad * (d.d / d.g) + kBlock - 1) / kBlock;
   if (grid > 0x7fffffff || fgrid > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "M too large");
   a.mblocks = int(mblocks);
   a.rblocks = int(rblocks);
-  void* args[] = {&a};
+  void* args[] = {&a, &p};
   hipError_t e = hipLaunchKernel(kern::stage1m(), dim3(unsigned(grid)), dim3(kS1MBlock), args, 0, s);
   if (e == hipSuccess)
     e = hipLaunchKernel(kern::stage1m_fin(), dim3(unsigned(fgrid)), dim3(kBlock), args, 0, s);
@@ -1235,7 +1248,12 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
   const WsLayout w = ws_layout(h, M, ARCHEAD_OP_TOPK);
   char* base = static_cast<char*>(ws);
   hipError_t e;
-  if (w.tk_fused) {
+  // One token: lists kept by the GEMV's own workgroups and their merge for a
+  // few entries, whose cost grows with k (us per call at k = 1 / 10 / 50: Qwen
+  // head 61.4 / 75.4 / 127, 8192-row head 14.7 / 23.7 / 65.8); else the logits
+  // and the top-k of rows, whose cost hardly does (67 / 68.6 / 71.8 and
+  // 20 / 21 / 23.3).
+  if (w.tk_fused && k <= kTopKFusedK) {
     float* pv = reinterpret_cast<float*>(base + w.tk_pv_off);
     int* pi = reinterpret_cast<int*>(base + w.tk_pi_off);
     int64_t np = w.n_part;
@@ -1260,9 +1278,9 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
     int64_t ldl = V;
     uint32_t* keys = reinterpret_cast<uint32_t*>(base + w.tk_key_off);
     int cs = w.tk_cs, nc = w.tk_n_chunk;
-    constexpr int kPerWg = kWaves * kTopKWaveChunks;
+    const int per_wg = kWaves * (cs < kTopKWave ? kTopKWave / cs : 1);
     void* xargs[] = {&lg, &ldl, const_cast<int64_t*>(&V), &cs, &nc, &keys};
-    e = hipLaunchKernel(kern::topk_max(), dim3(unsigned((nc + kPerWg - 1) / kPerWg), unsigned(mc)),
+    e = hipLaunchKernel(kern::topk_max(cs), dim3(unsigned((nc + per_wg - 1) / per_wg), unsigned(mc)),
                         dim3(kBlock), xargs, 0, s);
     if (e != hipSuccess) return hip_fail(e, "top-k chunk maxima launch");
     float* vo = vals ? vals + m0 * ldk : nullptr;

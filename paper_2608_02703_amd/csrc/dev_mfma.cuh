@@ -765,6 +765,7 @@ struct PrepArgs {
   int8_t* ucodes;
   int cu_row;            // bytes per row of U_c (r_c int8 codes, or ARCHEAD_I5 words)
   int u5;                // U_c codes are ARCHEAD_I5 words
+  int blocks;            // k_stage1m: leading workgroups that build the tables
 };
 
 __device__ __forceinline__ float nz_scale(uint16_t h) {

@@ -47,10 +47,11 @@ constexpr int kMidWindow = 256;           // elements of d per x window of that 
 constexpr int kMidWaveCount = 8;          // its waves per workgroup
 constexpr int kTopKMaxK = 64;             // largest k of archead_logits_topk (lanes of a wave)
 constexpr int64_t kTopKChunk = 256;       // tokens per chunk of the unfused top-k
-// the unfused top-k's chunks of a row of logits: at most kTopKChunks, of a
-// power of two times kTopKChunkUnit logits; a wave of the first kernel takes
-// kTopKWaveChunks
-constexpr int kTopKChunks = 1024, kTopKChunkUnit = 256, kTopKWaveChunks = 4;
+// the unfused top-k's chunks of a row of logits: at most kTopKChunks, of
+// kTopKChunkUnit logits, four times that, or a power of two times kTopKWave,
+// which a wave of the first kernel takes at a time
+constexpr int kTopKChunks = 1024, kTopKChunkUnit = 64, kTopKWave = 1024;
+constexpr int kTopKFusedK = 6;            // largest k of the fused single-token top-k
 constexpr int kTopKMergeBlock = 1024;     // threads of the round-based top-k merge workgroup
 constexpr int kTopKMergeC = 8;            // candidates per thread of that merge (else the scan merge)
 

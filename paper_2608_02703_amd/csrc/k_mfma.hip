@@ -5,9 +5,10 @@
 
 namespace {
 
-__global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
-  const int64_t nthr = int64_t(gridDim.x) * kBlock;
-  const int64_t t0 = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+// The head-derived tables, by thread t0 of nthr.  What bounds it: latency;
+// so a column's scales are read eight at a time, ahead of the stores (one at a
+// time 50 us for the 151936-row head).
+__device__ __forceinline__ void prep_tables(const PrepArgs& a, int64_t t0, int64_t nthr) {
   // (a) one thread per (vocabulary tile, column): walk the slots of the row
   // (lanes write consecutive columns)
   for (int64_t e = t0; e < a.n_vt * kTN; e += nthr) {
@@ -16,41 +17,51 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
     const uint16_t* src = a.rs + v * a.ngrp;
     const uint8_t* src8 = reinterpret_cast<const uint8_t*>(a.rs) + v * a.ngrp;
     const float rsv = a.rrs ? f16_to_f32(a.rrs[v]) : 0.f;
+    const float su = a.rc ? nz_scale(a.su[v]) : 0.f, sa = a.rr ? nz_scale(a.sa[v]) : 0.f;
     float* dst = a.ratio + vt * int64_t(a.nslot) * kTN + c;
     float prev = 0.f;
     int k = 0;
-    for (; k < a.ngrp; ++k) {
-      float s;
-      if (a.rrs) {   // rs * q, exact in fp32
-        s = rsv * float(src8[k]);
-        s = s == 0.f ? kZeroScale : s;
-      } else {
-        s = nz_scale(src[k]);
+    constexpr int kAhead = 8;
+    for (int k0 = 0; k0 < a.ngrp; k0 += kAhead) {
+      float s[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int j = k0 + u < a.ngrp ? k0 + u : a.ngrp - 1;
+        if (a.rrs) {   // rs * q, exact in fp32
+          s[u] = rsv * float(src8[j]);
+          s[u] = s[u] == 0.f ? kZeroScale : s[u];
+        } else {
+          s[u] = nz_scale(src[j]);
+        }
       }
-      dst[int64_t(k) * kTN] = k ? prev / s : 0.f;
-      prev = s;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (k0 + u >= a.ngrp) break;
+        dst[int64_t(k) * kTN] = k ? prev / s[u] : 0.f;
+        prev = s[u];
+        ++k;
+      }
     }
     if (a.rc) {
-      const float s = nz_scale(a.su[v]);
-      dst[int64_t(k++) * kTN] = prev / s;
-      prev = s;
+      dst[int64_t(k++) * kTN] = prev / su;
+      prev = su;
     }
     if (a.rr) {
-      const float s = nz_scale(a.sa[v]);
-      dst[int64_t(k++) * kTN] = prev / s;
-      prev = s;
+      dst[int64_t(k++) * kTN] = prev / sa;
+      prev = sa;
     }
     a.fin[vt * kTN + c] = prev * ldexpf(1.f, -(kXExp + kCodeExp));
   }
-  // (b) 16 bytes per thread (row-major, so lanes write consecutive chunks)
-  const int64_t n16 = a.V * (a.urow / 16);
-  for (int64_t e = t0; e < n16; e += nthr) {
-    const int64_t v = e / (a.urow / 16);
-    const int j0 = int(e % (a.urow / 16)) * 16;
+  // (b) 16 dimensions per thread, stored twice (row-major, so lanes write
+  // consecutive chunks)
+  const int nch = a.urow / 32;
+  for (int64_t e = t0; e < a.V * nch; e += nthr) {
+    const int64_t v = e / nch;
+    const int j0 = int(e % nch) * kExpDims;
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj) {
-      const int j = (j0 / 32) * 16 + jj;   // dimension (both copies of a block)
+      const int j = j0 + jj;
       int8_t c = 0;
       if (j < a.rc_pad) {
         if (j < a.rc)
@@ -60,8 +71,13 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
       }
       w[jj / 4] |= uint32_t(uint8_t(c)) << (8 * (jj % 4));
     }
-    *reinterpret_cast<uint4*>(a.ucodes + v * a.urow + j0) = make_uint4(w[0], w[1], w[2], w[3]);
+    uint4* dst = reinterpret_cast<uint4*>(a.ucodes + e * 32);
+    dst[0] = dst[1] = make_uint4(w[0], w[1], w[2], w[3]);
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
+  prep_tables(a, int64_t(blockIdx.x) * kBlock + threadIdx.x, int64_t(gridDim.x) * kBlock);
 }
 
 // One token's scaled x (a workgroup).
@@ -95,18 +111,26 @@ __device__ __forceinline__ void scale_row(const Stage1MArgs& a, int64_t m, int* 
   if (threadIdx.x == 0) a.rowexp[m] = ldexpf(1.f, e);
 }
 
-__global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a) {
+// The first p.blocks workgroups build the head-derived tables (a head used
+// without prepared ones): the two are independent and each too short to fill
+// the chip.
+__global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a, PrepArgs p) {
   __shared__ float red[kS1MWaves][kS1MTok][kS1MCols + 1];
+  if (int(blockIdx.x) < p.blocks) {
+    prep_tables(p, int64_t(blockIdx.x) * kS1MBlock + threadIdx.x, int64_t(p.blocks) * kS1MBlock);
+    return;
+  }
+  const int wg = int(blockIdx.x) - p.blocks;
   const int64_t n_s1 = int64_t(a.mblocks) * a.rblocks * a.ksplit;
-  if (int64_t(blockIdx.x) >= n_s1) {
-    scale_row(a, int64_t(blockIdx.x) - n_s1, reinterpret_cast<int*>(&red[0][0][0]));
+  if (wg >= n_s1) {
+    scale_row(a, wg - n_s1, reinterpret_cast<int*>(&red[0][0][0]));
     return;
   }
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, q = lane >> 4;
   const int R = a.rc + a.rr;
-  const int bx = int(blockIdx.x) % a.mblocks, byz = int(blockIdx.x) / a.mblocks;
+  const int bx = wg % a.mblocks, byz = wg / a.mblocks;
   const int by = byz % a.rblocks;
   const int64_t tok0 = int64_t(bx) * kS1MTok;
   const int kb = by * kS1MCols;           // first factor row of this workgroup

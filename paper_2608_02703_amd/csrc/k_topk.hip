@@ -100,38 +100,39 @@ __device__ __forceinline__ uint32_t tk_key(float v) {
   return v != v ? 0u : (u & 0x80000000u ? ~u : u | 0x80000000u);
 }
 
-constexpr int kChunkUnit = 256;          // logits a wave takes at a time
+constexpr int kChunkUnit = 64;           // logits a wave takes per load
 constexpr int kSelBlock = 1024, kSelWaves = kSelBlock / 64;
-constexpr int kSelCand = 2048;           // candidates held; more take the list scan
-constexpr int kMaxWaveChunks = 4;        // chunks per wave of k_topk_max
+constexpr int kSelCand = 4096;           // candidates held; more take the list scan
+constexpr int kWaveUnits = 16;           // units a wave of k_topk_max takes at a time
+constexpr int kSelUnits = 8;             // units a wave of k_topk_select has in flight
 static_assert(archead::kTopKChunks == kSelBlock && archead::kTopKChunkUnit == kChunkUnit &&
-              archead::kTopKWaveChunks == kMaxWaveChunks, "host and kernels agree on the chunks");
+              archead::kTopKWave == kChunkUnit * kWaveUnits, "host and kernels agree on the chunks");
 
-// Grid (ceil(n_chunk / (kWaves kMaxWaveChunks)), tokens): keys[m][c] = the
-// largest key of logits [c cs, (c + 1) cs) of row m.
+// keys[m][c] = the largest key of logits [c cs, (c + 1) cs) of row m.  UPC:
+// units per chunk, or kWaveUnits for chunks of any multiple of them; a wave
+// takes kWaveUnits / UPC chunks.
+template <int UPC>
 __global__ __launch_bounds__(kBlock) void k_topk_max(const float* logits, int64_t ldl, int64_t V, int cs,
                                                      int n_chunk, uint32_t* keys) {
+  constexpr int kCpw = kWaveUnits / UPC;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int64_t m = blockIdx.y;
   const float* row = logits + m * ldl;
-  const int c0 = (int(blockIdx.x) * kWaves + wid) * kMaxWaveChunks;
-  uint32_t best[kMaxWaveChunks] = {};
-  for (int o = 0; o < cs; o += kChunkUnit) {
-    float v[kMaxWaveChunks][4];
+  const int c0 = (int(blockIdx.x) * kWaves + wid) * kCpw;
+  const int span = UPC < kWaveUnits ? kWaveUnits * kChunkUnit : cs;
+  uint32_t best[kCpw] = {};
+  for (int o = 0; o < span; o += kWaveUnits * kChunkUnit) {
+    float v[kWaveUnits];
 #pragma unroll
-    for (int c = 0; c < kMaxWaveChunks; ++c)
+    for (int u = 0; u < kWaveUnits; ++u) {
+      const int64_t j = int64_t(c0) * cs + o + u * kChunkUnit + lane;
+      v[u] = j < V ? row[j] : NAN;
+    }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t j = int64_t(c0 + c) * cs + o + 64 * u + lane;
-        v[c][u] = j < V ? row[j] : NAN;
-      }
-#pragma unroll
-    for (int c = 0; c < kMaxWaveChunks; ++c)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) best[c] = max(best[c], tk_key(v[c][u]));
+    for (int u = 0; u < kWaveUnits; ++u) best[u / UPC] = max(best[u / UPC], tk_key(v[u]));
   }
 #pragma unroll
-  for (int c = 0; c < kMaxWaveChunks; ++c) {
+  for (int c = 0; c < kCpw; ++c) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) best[c] = max(best[c], uint32_t(__shfl_xor(int(best[c]), off, 64)));
     if (lane == 0 && c0 + c < n_chunk) keys[m * n_chunk + c0 + c] = best[c];
@@ -183,34 +184,29 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
   const uint32_t fl = sfloor;
   if (mine >= fl) slist[atomicAdd(&nlist, 1)] = tid;
   __syncthreads();
-  const int upc = cs / kChunkUnit, units = nlist * upc;
-  constexpr int kBatch = 4;   // units of a wave in flight
-  for (int u0 = wid; u0 < units; u0 += kBatch * kSelWaves) {
-    float v[kBatch][4];
-    int64_t j0[kBatch];
+  const int lu = __builtin_ctz(cs / kChunkUnit), units = nlist << lu;   // (a power of two)
+  for (int u0 = wid; u0 < units; u0 += kSelUnits * kSelWaves) {
+    float v[kSelUnits];
+    int64_t j[kSelUnits];
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
+    for (int b = 0; b < kSelUnits; ++b) {
       const int u = u0 + b * kSelWaves;
-      const bool on = u < units;
-      j0[b] = on ? int64_t(slist[u / upc]) * cs + int64_t(u % upc) * kChunkUnit + lane : V;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[b][q] = j0[b] + 64 * q < V ? row[j0[b] + 64 * q] : NAN;
+      j[b] = u < units ? int64_t(slist[u >> lu]) * cs + (u & ((1 << lu) - 1)) * kChunkUnit + lane : V;
+      v[b] = j[b] < V ? row[j[b]] : NAN;
     }
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const bool hit = tk_key(v[b][q]) >= fl;
-        const uint64_t mask = __ballot(hit);
-        if (!mask) continue;
-        int at = 0;
-        if (lane == 0) at = atomicAdd(&ncand, __popcll(mask));
-        at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((uint64_t(1) << lane) - 1));
-        if (hit && at < kSelCand) {
-          cval[at] = v[b][q];
-          cidx[at] = int(j0[b] + 64 * q);
-        }
+    for (int b = 0; b < kSelUnits; ++b) {
+      const bool hit = tk_key(v[b]) >= fl;
+      const uint64_t mask = __ballot(hit);
+      if (!mask) continue;
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&ncand, __popcll(mask));
+      at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((uint64_t(1) << lane) - 1));
+      if (hit && at < kSelCand) {
+        cval[at] = v[b];
+        cidx[at] = int(j[b]);
       }
+    }
   }
   __syncthreads();
   const int nc = ncand;
@@ -377,7 +373,11 @@ const void* gemv_topk(int lpr, bool sc8, int gen) {
   return gemv_topk_fn<0>(lpr, sc8);
 }
 
-const void* topk_max() { return reinterpret_cast<const void*>(k_topk_max); }
+const void* topk_max(int cs) {
+  return cs == kChunkUnit       ? reinterpret_cast<const void*>(k_topk_max<1>)
+         : cs == 4 * kChunkUnit ? reinterpret_cast<const void*>(k_topk_max<4>)
+                                : reinterpret_cast<const void*>(k_topk_max<kWaveUnits>);
+}
 const void* topk_select() { return reinterpret_cast<const void*>(k_topk_select); }
 const void* topk_merge(int block) {
   return block == 256 ? reinterpret_cast<const void*>(k_topk_merge<256>)

@@ -15,7 +15,7 @@ const void* gemv(int tok, int lpr, bool ce, bool sc8, int gen);
 // SC8, GEN, true>; null where gemv has no such variant), the merge of its
 // per-workgroup lists, and the top-k of rows of fp32 logits in two kernels
 const void* gemv_topk(int lpr, bool sc8, int gen);
-const void* topk_max();      // the maxima of the rows' chunks, then
+const void* topk_max(int cs);      // the maxima of the rows' chunks, then
 const void* topk_select();   // the k best from the chunks that can hold one
 const void* topk_merge(int block);   // k rounds; workgroups of 256 or kTopKMergeBlock threads, kTopKMergeC candidates each
 const void* topk_merge_scan();   // any number of candidates
