@@ -386,9 +386,9 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 constexpr int kTM = 256, kTN = 256;          // tile: tokens x vocabulary rows
-constexpr int kMBlock = 512, kMWaves = 8;    // 2 x 4 waves of 128 x 64
+constexpr int kMWaves = 8;                   // 2 x 4 waves of 128 x 64
 constexpr int kKS = 64;                      // K elements per stage
-constexpr int kRing = 3;                     // LDS stages (two loads in flight)
+constexpr int kRing = 3;                     // LDS stages: one computed, one landed, one on its way
 constexpr int kRasterGM = 4;                 // token tiles per raster group (measured: 2 and 8 slower at M = 4096)
 constexpr float kZeroScale = 0x1p-60f;       // stand-in for a zero scale
 // Scaling of the tiled kernel's operands (powers of two, so nothing rounds):

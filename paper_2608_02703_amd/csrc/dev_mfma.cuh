@@ -8,17 +8,16 @@ namespace {
 
 // ------------------------------------------------------------ many tokens: MFMA
 // Tiled bf16 MFMA path for many tokens (needs g % 64 == 0).  A workgroup owns
-// a kTM x kTN tile (tokens x vocabulary rows); its eight waves own 128 x 64
-// blocks (2 along the tokens, 4 along the vocabulary), each an 8 x 4 grid of
-// 16x16 MFMA tiles (v_mfma_f32_16x16x32_bf16: A lane l holds row l%16 and 8
-// k-slots of quarter l/16; B likewise by column; D lane l holds rows
-// 4 (l/16) .. +3 of column l%16).  The K loop runs in stages of kKS elements
-// that direct global-to-LDS buffer loads bring into a ring of kRing LDS
-// stages, two stages ahead of the compute, with no register staging.  Within
-// a stage lane quarter q takes code dwords 2q, 2q+1 (one per MFMA K-chunk)
-// and the x chunks with the same indices, so its codes are one 8-byte read.
-// Token rows and vocabulary rows are XOR-swizzled in 16-byte units so
-// fragment reads are bank-conflict free.
+// a TM x kTN tile (tokens x vocabulary rows), its waves blocks of WM x 64, each
+// a grid of 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16: lane l holds row l%32
+// of an operand and 8 k-slots of half l/32; D lane l holds column l%32, rows
+// 8 (i/4) + 4 (l/32) + i%4).  The K loop runs in stages of kKS elements that
+// direct global-to-LDS buffer loads bring, with no register staging: x into a
+// ring of kRing stages, the codes of two stages into one place, which every
+// wave empties into registers before the stage that uses them.  Within a
+// stage half-wave h takes the row's code dwords 4h .. 4h + 3 (one 16-byte
+// read) and the x units of the same indices.  Token rows and vocabulary rows
+// are XOR-swizzled in 16-byte units so fragment reads are bank-conflict free.
 //
 // Codes are unpacked per wave to bf16 u 2^-133, u = c + 8 (exact,
 // unpack8_sub), against x scaled per token by a power of two (kXExp) and, at
@@ -36,14 +35,20 @@ namespace {
 // fp32 precision) as [hi | mid | lo | 0], the "code" rows the int8 factor
 // codes (exact in bf16) twice, [c | c]; one K-step per part.
 //
-// What bounds it: the matrix unit and the VALU share the SIMD's time (a
-// 32-cycle MFMA hides about four VALU operations of either resident wave;
-// more lengthen it), and the chip runs at its power limit (about 1.7-1.8 GHz
-// under this load), so the loop is built for few VALU operations per MFMA:
-// 1.25 for the unpack and 2 for the rescale (one FMA per element and group of
-// 128).  The codes are the MFMA's first operand, so a lane holds the logits of
-// one token: the biases are one LDS word per token block, and the softmax
-// epilogues reduce within the lane.
+// What bounds it.  Many tokens: the matrix unit and the VALU share the SIMD's
+// time (a 32-cycle MFMA hides about four VALU operations of either resident
+// wave; more lengthen it), and the chip runs at its power limit (about 1.65-1.75
+// GHz under this load, falling as the matrix unit gets busier), so the loop is
+// built for few VALU operations per MFMA: 1.25 for the unpack and 2 for the
+// rescale (one FMA per element and group of 128).  The codes are the MFMA's
+// first operand, so a lane holds the logits of one token: the biases are one
+// LDS word per token block, and the softmax epilogues reduce within the lane.
+// Against 16x16x32 MFMAs with lanes along the vocabulary, magic-number codes
+// and the barrier between stages (us per call): Qwen CE M = 4096 4943 -> 4603,
+// 128k head M = 512 1052 -> 1015; matrix unit busy 54 / 59% -> 62 / 63%.
+// Few tokens: the stream of codes, and in it the size of the pieces: 64 bytes
+// of a row at a time instead of 32 took the Qwen head at M = 64 from 142 to
+// 128.5 us per call (117 us in this kernel, 2.9 TB/s), M = 512 from 619 to 603.
 struct MfmaArgs {
   const uint8_t* codes;
   const uint16_t* x;       // [M][ldx] bf16, scaled (Stage1MArgs::xs)
