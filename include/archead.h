@@ -188,8 +188,8 @@ void archead_destroy(archead_handle* h);
  * decode and several-token paths with a 32-bit call stamp beside each value; on the tiled
  * MFMA path split into three bf16 parts), on the tiled path also a copy of x
  * (2 * M * d bytes, each token scaled by a power of two) and per-call
- * tables derived from the head (group-scale ratios, the per-group sums of x,
- * the factor codes as bf16 and the U_c / A_w codes side by side: about
+ * tables derived from the head (group-scale ratios, the U_c / A_w codes side
+ * by side) and the per-group sums of x (the tables: about
  * V * (r_c + r_r + 4 * (d/g + 3)) bytes, used only while the head has no
  * prepared buffer, see archead_prepare), and for the CE call the
  * per-vocabulary-tile softmax partials.  Returns 0 for a NULL handle or

@@ -485,7 +485,7 @@ char* prep_base(const archead_handle* h, const WsLayout& w, char* ws) {
 }
 
 // The head-derived tables (tile-major residual scale ratios, final scales,
-// bf16 factor codes of V_c / B_w, paired U_c / A_w codes) into the block at
+// paired U_c / A_w codes) into the block at
 // base, laid out as prep_layout says.
 PrepArgs prep_args(const archead_handle* h, char* base) {
   const archead_desc& d = h->desc;

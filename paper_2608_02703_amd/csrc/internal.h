@@ -124,7 +124,7 @@ WsLayout ws_layout_path(const archead_handle* h, int64_t M, archead_op op, Path 
                         int64_t call_M = 0);
 
 // The many-token kernel's tables that depend on the head only (scale
-// ratios, final scales, bf16 V_c / B_w codes, paired U_c / A_w codes):
+// ratios, final scales, paired U_c / A_w codes):
 // offsets from the start of their block, in the workspace or in a prepared
 // buffer (the same layout in both).
 struct PrepLayout {
