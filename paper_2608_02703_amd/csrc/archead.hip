@@ -338,12 +338,13 @@ static WsLayout topk_layout(const archead_handle* h, int64_t M) {
   w.tk_lg_off = off;
   off = align256(off + sizeof(float) * size_t(chunk) * size_t(d.V));
   w.tk_in_off = off;
-  // every chunk runs on the kernel the whole call would take, so the
-  // logits are those archead_logits gives for the same M
+  // every chunk runs on the kernel the whole call would take, with its split
+  // of stage 1 along d, so the logits are those archead_logits gives for the
+  // same M
   w.tk_path = choose_path(h, M);
-  size_t inner = ws_layout_path(h, chunk, ARCHEAD_OP_LOGITS, w.tk_path).total;
+  size_t inner = ws_layout_path(h, chunk, ARCHEAD_OP_LOGITS, w.tk_path, M).total;
   if (M % chunk) {
-    const size_t t = ws_layout_path(h, M % chunk, ARCHEAD_OP_LOGITS, w.tk_path).total;
+    const size_t t = ws_layout_path(h, M % chunk, ARCHEAD_OP_LOGITS, w.tk_path, M).total;
     inner = t > inner ? t : inner;
   }
   off = align256(off + inner);
@@ -1273,7 +1274,7 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
   for (int64_t m0 = 0; m0 < M; m0 += w.tk_chunk) {
     const int64_t mc = M - m0 < w.tk_chunk ? M - m0 : w.tk_chunk;
     st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, mc, ldx, lg, ARCHEAD_F32, V,
-                    base + w.tk_in_off, s, w.tk_path);
+                    base + w.tk_in_off, s, w.tk_path, M);
     if (st != ARCHEAD_OK) return st;
     int64_t ldl = V;
     uint32_t* keys = reinterpret_cast<uint32_t*>(base + w.tk_key_off);

@@ -210,3 +210,19 @@ def test_topk_chunk_edges(V):
                         assert np.array_equal(vals[m].view(np.uint32), wv.view(np.uint32))
         finally:
             ph.close()
+
+
+@pytest.mark.parametrize("M,d", [(2100, 2048), (4100, 1024)])
+def test_topk_of_chunks_selects_over_the_whole_calls_logits(M, d):
+    """A call of several chunks of tokens selects over archead_logits' values
+    for the same M, bit for bit, also where stage 1 of a chunk alone would be
+    split along d otherwise (here 4 and 2 ways in a chunk of 256 tokens, 2 and
+    1 ways in the call, which has 132 and 257 blocks of 16 tokens)."""
+    from paper_2608_02703_amd import PackedHead
+    h = make_head("tiny", V=256, d=d, g=64, rc=20, rr=0)
+    ph = PackedHead.from_arrays(h)
+    try:
+        say(f"top-k chunks M={M}")
+        _check(ph, make_x("tiny", M, d=d), 10, what=f"chunks M={M}")
+    finally:
+        ph.close()
