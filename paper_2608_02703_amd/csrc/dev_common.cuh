@@ -394,11 +394,14 @@ constexpr float kZeroScale = 0x1p-60f;       // stand-in for a zero scale
 // Scaling of the tiled kernel's operands (powers of two, so nothing rounds):
 // a token's x is multiplied by 2^(kXExp - e), e the exponent of its largest
 // magnitude; the codes are worth 2^-133 (unpack8_sub), so the accumulator is
-// 2^(kXExp - e - 133) times the logit over the slot's scale.  kXExp = 64 keeps
-// 24 bits above fp32's smallest subnormal for scale ratios of 2^40 (the fp16
-// range), and the fidelity pass's dense sums below overflow to logits of
-// 2^(63 + e).
-constexpr int kXExp = 64;
+// 2^(kXExp - e - 133) times the logit over the slot's scale.  The larger kXExp,
+// the smaller the logits (against their token's largest magnitude) that keep
+// their bits: 112 keeps 24 of them down to 2^-105 times 2^e and that scale,
+// and the largest sum there is (rank 2^14, a factor part of scale 2^16 before
+// one of scale zero, kZeroScale) is 2^114.  The fidelity pass, whose dense sums
+// take the same x, scales by less: they overflow at logits of 2^(63 + e), and
+// the packed ones keep 24 bits down to 2^-57.
+constexpr int kXExp = 112, kXExpFid = 64;
 constexpr int kCodeExp = -133;
 constexpr int kSteps = kKS / 16;             // MFMA K-steps per stage
 constexpr int kExpParts = 3;                 // K-steps of an expansion stage: the parts of t

@@ -20,9 +20,10 @@ namespace {
 // are XOR-swizzled in 16-byte units so fragment reads are bank-conflict free.
 //
 // Codes are unpacked per wave to bf16 u 2^-133, u = c + 8 (exact,
-// unpack8_sub), against x scaled per token by a power of two (kXExp) and, at
-// the elements of the odd code pairs, by 1 / 16.  The accumulator is kept in
-// units of the current scale slot's scale: at the start of slot k it becomes
+// unpack8_sub), against x scaled per token by a power of two (kXExp; in the
+// fidelity and rank passes kXExpFid) and, at the elements of the odd code
+// pairs, by 1 / 16.  The accumulator is kept in units of the current scale
+// slot's scale: at the start of slot k it becomes
 // acc * (s'_{k-1} / s'_k) + bias_k, after which the MFMAs add the slot's
 // terms, so at the end s'_last * acc is the scaled logit.  Slots are the
 // residual groups (bias -8 * (sum of x over the group), the MFMAs adding
@@ -468,20 +469,22 @@ void k_mfma(MfmaArgs a) {
     if (s + 1 < ntot) exp_stage(s + 1, kAny{}, Odd{});
   }
 
-  // the last slot's scales and the token's power of two (dense sums: without
-  // the scale, and 2^-kXExp apart, as 2^(e - kXExp) may be below fp32's range)
+  // the last slot's scales and the token's power of two (fidelity and rank:
+  // the scales hold 2^-kXExp; dense sums: without the scale, and 2^-kXExpFid
+  // apart, as 2^(e - kXExpFid) may be below fp32's range)
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const f32x4_t fin = *reinterpret_cast<const f32x4_t*>(a.fin + vt * kTN + G::WN * wn + 32 * ni + 8 * k + 4 * h);
+      f32x4_t fin = *reinterpret_cast<const f32x4_t*>(a.fin + vt * kTN + G::WN * wn + 32 * ni + 8 * k + 4 * h);
+      if constexpr (XE != 0) fin *= ldexpf(1.f, kXExp - kXExpFid);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           acc[mi][ni][4 * k + i] = acc[mi][ni][4 * k + i] * fin[i] * rf[mi];
           if constexpr (XE == 1)
-            accd[mi][ni][4 * k + i] = accd[mi][ni][4 * k + i] * ldexpf(1.f, -kXExp) * rf[mi];
+            accd[mi][ni][4 * k + i] = accd[mi][ni][4 * k + i] * ldexpf(1.f, -kXExpFid) * rf[mi];
         }
     }
 
@@ -789,9 +792,9 @@ __device__ __forceinline__ float nz_scale(uint16_t h) {
 // sums of x; the eight partial results are summed in LDS in a fixed order.
 // The launch's further workgroups each scale one token's x for the tiled
 // kernel: xs = x 2^(kXExp - e), e the exponent of the row's largest magnitude
-// (rowexp = 2^e), and unless `even` another 2^-4 at elements 2, 3, 6, 7 of
-// every 8 (the odd code pairs; exact).  k_stage1m_fin: with that scale and
-// the codes' 2^kCodeExp, t as three bf16 parts hi, mid, lo, laid out per block
+// (rowexp = 2^e), and another 2^-4 at elements 2, 3, 6, 7 of every 8 (the odd
+// code pairs; exact); for the passes that read a dense head (`even`) xs = x
+// 2^(kXExpFid - e).  k_stage1m_fin: with that scale and the codes' 2^kCodeExp, t as three bf16 parts hi, mid, lo, laid out per block
 // of 16 rank dimensions as [hi | mid | lo | 0], the U_c part's blocks first,
 // each part zero-padded to whole blocks, and the slot biases -8 * (sum of x).
 struct Stage1MArgs {

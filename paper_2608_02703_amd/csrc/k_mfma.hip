@@ -101,7 +101,7 @@ __device__ __forceinline__ void scale_row(const Stage1MArgs& a, int64_t m, int* 
     u32x4_t v = *reinterpret_cast<const u32x4_t*>(x + i);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int k = kXExp - e - (!a.even && (j & 1) ? 4 : 0);
+      const int k = a.even ? kXExpFid - e : kXExp - e - (j & 1 ? 4 : 0);
       const uint32_t lo = __float_as_uint(ldexpf(bf16_lo(v[j]), k));
       const uint32_t hi = __float_as_uint(ldexpf(bf16_hi(v[j]), k));
       v[j] = (lo >> 16) | (hi & 0xffff0000u);
@@ -228,6 +228,7 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a, PrepArgs p
 __global__ __launch_bounds__(kBlock) void k_stage1m_fin(Stage1MArgs a) {
   const int R = a.rc + a.rr, ngrp = a.d / a.g, dims = a.nch * kExpDims;
   int64_t t = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const int scale_exp = (a.even ? kXExpFid : kXExp) + kCodeExp;
   auto exponent = [&](int64_t m) { return int(__float_as_uint(a.rowexp[m]) >> 23) - 127; };
   if (t < a.M * dims) {
     const int64_t m = t / dims;
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(kBlock) void k_stage1m_fin(Stage1MArgs a) {
       const int k = c < a.nch_u ? dim : a.rc + dim;
       float v = a.tpart[m * R + k];
       for (int ks = 1; ks < a.ksplit; ++ks) v += a.tpart[(int64_t(ks) * a.M + m) * R + k];
-      v = ldexpf(v, kXExp + kCodeExp - exponent(m));
+      v = ldexpf(v, scale_exp - exponent(m));
       hi = (__bf16)v;
       const float r1 = v - float(hi);
       md = (__bf16)r1;
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(kBlock) void k_stage1m_fin(Stage1MArgs a) {
   const int64_t m = t % mp, j = t / mp;
   if (j >= ngrp) return;
   a.gbias[((m / kTM) * ngrp + j) * kTM + m % kTM] =
-      m < a.M ? -8.f * ldexpf(a.gsum[j * a.M + m], kXExp + kCodeExp - exponent(m)) : 0.f;
+      m < a.M ? -8.f * ldexpf(a.gsum[j * a.M + m], scale_exp - exponent(m)) : 0.f;
 }
 
 }  // namespace

@@ -84,6 +84,36 @@ def test_row_magnitudes(kw, M):
         ph.close()
 
 
+@pytest.mark.parametrize("low", [-40, -60, -75])
+def test_small_logits_beside_a_large_element(low):
+    """A token's logits keep their bits where its largest element meets only
+    codes of zero and the others are 2^low of it."""
+    from paper_2608_02703_amd import PackedHead
+    h = make_head("tiny", V=300, d=256, g=64, rc=16, rr=4)
+    codes = np.array(h.res_codes)
+    codes[:, 0] = codes[:, 0] & 0xF0 | 8       # element 0: code 0
+    h.res_codes[:] = codes
+    h.core_v[:, 0] = 0
+    h.corr_b[:, 0] = 0
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal((33, 256)) * 2.0 ** low
+    x[:, :64] = 0                              # (the large element's group holds nothing else)
+    x[:, 0] = 3.0
+    x = f64_to_bf16_bits(x)
+    ref = ohead.logits(h, x)
+    ph = PackedHead.from_arrays(h)
+    ph.force_path("tiled")
+    try:
+        say(f"tiled small logits 2^{low}")
+        o = ph.logits(torch_x(x))
+        torch.cuda.synchronize()
+        o = o.cpu().numpy().astype(np.float64)
+        err = np.linalg.norm(o - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= REL, f"{err.max():.2e}"
+    finally:
+        ph.close()
+
+
 def test_every_code_and_position():
     """One-hot rows read back every code value at every position of a word,
     exactly: the offset cancels, and x's extra 1 / 16 at the odd code pairs."""
