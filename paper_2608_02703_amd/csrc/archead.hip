@@ -574,10 +574,13 @@ archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int6
   if (grid > 0x7fffffff || fgrid > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "M too large");
   a.mblocks = int(mblocks);
   a.rblocks = int(rblocks);
+  // a launch takes fewer than 2^32 threads along x: rows of kGridX workgroups
+  auto dims = [](int64_t n) {
+    return n <= kGridX ? dim3(unsigned(n)) : dim3(unsigned(kGridX), unsigned((n + kGridX - 1) / kGridX));
+  };
   void* args[] = {&a, &p};
-  hipError_t e = hipLaunchKernel(kern::stage1m(), dim3(unsigned(grid)), dim3(kS1MBlock), args, 0, s);
-  if (e == hipSuccess)
-    e = hipLaunchKernel(kern::stage1m_fin(), dim3(unsigned(fgrid)), dim3(kBlock), args, 0, s);
+  hipError_t e = hipLaunchKernel(kern::stage1m(), dims(grid), dim3(kS1MBlock), args, 0, s);
+  if (e == hipSuccess) e = hipLaunchKernel(kern::stage1m_fin(), dims(fgrid), dim3(kBlock), args, 0, s);
   return e == hipSuccess ? ARCHEAD_OK : hip_fail(e, "stage-1 launch");
 }
 

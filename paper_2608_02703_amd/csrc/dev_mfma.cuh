@@ -821,5 +821,9 @@ struct Stage1MArgs {
 };
 
 constexpr int kS1MTok = 16, kS1MCols = 64, kS1MBlock = 512, kS1MWaves = kS1MBlock / 64;
+// Workgroups of the two launches along x; more go on along y (2^22 of
+// kS1MBlock threads stay below the 2^32 of a launch's dimension).
+constexpr int64_t kGridX = int64_t(1) << 22;
+__device__ __forceinline__ int64_t stage1_block() { return int64_t(blockIdx.y) * gridDim.x + blockIdx.x; }
 
 }  // namespace

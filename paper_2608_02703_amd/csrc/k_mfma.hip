@@ -116,14 +116,15 @@ __device__ __forceinline__ void scale_row(const Stage1MArgs& a, int64_t m, int* 
 // the chip.
 __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a, PrepArgs p) {
   __shared__ float red[kS1MWaves][kS1MTok][kS1MCols + 1];
-  if (int(blockIdx.x) < p.blocks) {
-    prep_tables(p, int64_t(blockIdx.x) * kS1MBlock + threadIdx.x, int64_t(p.blocks) * kS1MBlock);
+  const int64_t blk = stage1_block();
+  if (blk < p.blocks) {
+    prep_tables(p, blk * kS1MBlock + threadIdx.x, int64_t(p.blocks) * kS1MBlock);
     return;
   }
-  const int wg = int(blockIdx.x) - p.blocks;
+  const int wg = int(blk - p.blocks);
   const int64_t n_s1 = int64_t(a.mblocks) * a.rblocks * a.ksplit;
   if (wg >= n_s1) {
-    scale_row(a, wg - n_s1, reinterpret_cast<int*>(&red[0][0][0]));
+    if (wg - n_s1 < a.M) scale_row(a, wg - n_s1, reinterpret_cast<int*>(&red[0][0][0]));
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(kS1MBlock) void k_stage1m(Stage1MArgs a, PrepArgs p
 // (residual group, token of the padded count, tokens fastest).
 __global__ __launch_bounds__(kBlock) void k_stage1m_fin(Stage1MArgs a) {
   const int R = a.rc + a.rr, ngrp = a.d / a.g, dims = a.nch * kExpDims;
-  int64_t t = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  int64_t t = stage1_block() * kBlock + threadIdx.x;
   const int scale_exp = (a.even ? kXExpFid : kXExp) + kCodeExp;
   auto exponent = [&](int64_t m) { return int(__float_as_uint(a.rowexp[m]) >> 23) - 127; };
   if (t < a.M * dims) {
