@@ -463,6 +463,11 @@ __device__ __forceinline__ void wait_loads_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// No instruction is moved across this point by the compiler's scheduler: the
+// counted waits above rely on the order of the loads before them, which the
+// language does not give (a load to registers and one to LDS share nothing).
+__device__ __forceinline__ void pin_vmem_order() { __builtin_amdgcn_sched_barrier(0); }
+
 template <typename T>
 __device__ __forceinline__ T lds_load(const lds_u8* p) {
   return *reinterpret_cast<const __attribute__((address_space(3))) T*>(p);

@@ -286,7 +286,8 @@ void k_mfma(MfmaArgs a) {
   issue(0, 0);
 #pragma unroll
   for (int ci = 0; ci < G::NC; ++ci) issue_code(0, ci, kAny{});
-  if (ntot > 1) issue(1, 1);
+  pin_vmem_order();   // the first wait leaves the newest NX loads in flight: all of stage 1
+  issue(1, 1);
 
   // slot start: rescale to the slot's scale and (residual groups) add its bias
   auto rescale = [&](const lds_u8* base, auto residual) {
@@ -334,8 +335,7 @@ void k_mfma(MfmaArgs a) {
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) A[mi] = lds_load<bf16x8_t>(p + aoff[0] + mi * 64 * kKS);
   };
-  if (ntot > 1) wait_loads_barrier<G::NX>();   // stage 1 has at least NX loads in flight
-  else wait_loads_barrier<0>();
+  wait_loads_barrier<G::NX>();   // (there are two stages at least; stage 1 has at least NX loads in flight)
   load_codes();
   load_first(base);
   if constexpr (XE == 1) {
@@ -372,6 +372,9 @@ void k_mfma(MfmaArgs a) {
   auto main_stage = [&](int s, auto issue_kind, auto parity) {
     constexpr int PAR = decltype(parity)::value;
     const lds_u8* nbase = ring_next(base);
+    // the wait below counts the dense loads of K-steps 0 and 1 as the newest
+    // ones: none may be moved ahead of the loads to LDS of the stage before
+    if constexpr (XE == 1) pin_vmem_order();
     if (sg == 0) rescale(base, std::true_type{});
 #pragma unroll
     for (int t = 0; t < kSteps; ++t) {
