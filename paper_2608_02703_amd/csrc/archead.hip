@@ -530,11 +530,12 @@ archead_status launch_prep(const archead_handle* h, char* base, hipStream_t s) {
 }
 
 // MFMA path prologue: the head-derived tables (unless the head has them
-// prepared), then stage 1 (t, the slot biases and the scaled x; `even`: without
+// prepared, or not `tables`: the workspace holds them from the call's part
+// before), then stage 1 (t, the slot biases and the scaled x; `even`: without
 // the odd code pairs' 1 / 16, for the passes that read a dense head too).
 archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int64_t M,
                                     int64_t ldx, const WsLayout& w, char* ws, hipStream_t s,
-                                    bool even = false) {
+                                    bool even = false, bool tables = true) {
   const archead_desc& d = h->desc;
   const int R = int(d.r_c + d.r_r);
   // 256 rows of x span less than 2 GiB
@@ -542,7 +543,7 @@ archead_status launch_mfma_prologue(const archead_handle* h, const void* x, int6
     return fail(ARCHEAD_E_UNSUPPORTED, "ldx too large for the many-token kernel");
   PrepArgs p;
   memset(&p, 0, sizeof p);
-  if (!h->prep.load(std::memory_order_acquire)) {
+  if (tables && !h->prep.load(std::memory_order_acquire)) {
     p = prep_args(h, ws + w.rat_off);
     p.blocks = prep_blocks(h, p, kS1MBlock);
   }
@@ -929,12 +930,12 @@ archead_status launch_softmax_partials(const archead_handle* h, const void* x, i
 }
 
 // The logits of archead_logits after its checks (also the first half of
-// the unfused top-k).
+// the unfused top-k), with a workspace laid out as w says; tables: as
+// launch_mfma_prologue.
 archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
                           void* out, archead_dtype out_dtype, int64_t ldo, void* ws,
-                          hipStream_t s, Path path, int64_t call_M = 0) {
+                          hipStream_t s, Path path, const WsLayout& w, bool tables = true) {
   archead_status st = ARCHEAD_OK;
-  const WsLayout w = ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path, call_M);
   if (path == Path::kDec) {
     DecArgs a;
     memset(&a, 0, sizeof a);
@@ -956,7 +957,7 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
                       s);
   }
   if (path == Path::kTiled) {
-    st = launch_mfma_prologue(h, x, M, ldx, w, static_cast<char*>(ws), s);
+    st = launch_mfma_prologue(h, x, M, ldx, w, static_cast<char*>(ws), s, false, tables);
     if (st != ARCHEAD_OK) return st;
     MfmaArgs a = mfma_args(h, M, w, static_cast<char*>(ws));
     a.out = out;
@@ -976,17 +977,36 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
 
 namespace archead {
 
-size_t noalloc_bytes(const archead_handle* h, int64_t M) {
-  const Path path = choose_path(h, M);
-  if (path != Path::kTiled) return ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path).total;
+// The bytes a call of the tiled path is counted with, but for the partials of
+// a stage 1 split along d.
+static size_t noalloc_tiled_bytes(const archead_handle* h, int64_t M) {
   const archead_desc& d = h->desc;
   const size_t nch = size_t(exp_chunks(d.r_c) + exp_chunks(d.r_r));
   const size_t nslot = size_t(d.d / d.g) + (d.r_c ? 1 : 0) + (d.r_r ? 1 : 0);
   const size_t n_mt = size_t((M + kTM - 1) / kTM);
-  const int ks = s1_ksplit(h, M);
   return align256(sizeof(uint16_t) * size_t(M) * nch * 64) + align256(sizeof(float) * n_mt * nslot * kTM) +
-         prep_layout(h).total + align256(sizeof(uint16_t) * size_t(d.r_c + d.r_r) * size_t(d.d)) +
+         prep_layout(h).total + align256(sizeof(uint16_t) * size_t(d.r_c + d.r_r) * size_t(d.d));
+}
+
+size_t noalloc_bytes(const archead_handle* h, int64_t M) {
+  const Path path = choose_path(h, M);
+  if (path != Path::kTiled) return ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path).total;
+  const archead_desc& d = h->desc;
+  const int ks = s1_ksplit(h, M);
+  return noalloc_tiled_bytes(h, M) +
          (ks > 1 ? align256(sizeof(float) * size_t(ks) * size_t(M) * size_t(d.r_c + d.r_r)) : 0);
+}
+
+size_t noalloc_call_bytes(const archead_handle* h, int64_t M) {
+  return ws_layout_path(h, M, ARCHEAD_OP_LOGITS, choose_path(h, M)).total;
+}
+
+bool noalloc_wants(const archead_handle* h, size_t beyond) {
+  if (!mfma_ok(h)) return false;
+  // the first token count, by doubling, whose tiled call takes more
+  int64_t M = 1;
+  while (ws_layout_path(h, M, ARCHEAD_OP_LOGITS, Path::kTiled).total <= beyond) M *= 2;
+  return noalloc_tiled_bytes(h, (M + 1) / 2) <= size_t(ARCHEAD_NOALLOC_SCRATCH_BYTES);
 }
 
 archead_status logits_in_chunks(const archead_handle* h, const void* x, int64_t M, int64_t ldx, void* out,
@@ -997,15 +1017,28 @@ archead_status logits_in_chunks(const archead_handle* h, const void* x, int64_t 
   st = check_out(h, out, out_dtype, ldo);
   if (st != ARCHEAD_OK) return st;
   const Path path = choose_path(h, M);
+  auto need = [&](int64_t m) { return ws_layout_path(h, m, ARCHEAD_OP_LOGITS, path, M).total; };
   int64_t mc = M;
-  while (mc > 1 && ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, path, M).total > ws_bytes) mc = (mc + 1) / 2;
-  const size_t need = ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, path, M).total;
-  if (need > ws_bytes) return fail(ARCHEAD_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
+  if (need(M) > ws_bytes) {
+    // the most tokens that fit, then as few chunks of about the same size, of
+    // whole 256-token tiles where that many fit
+    int64_t lo = 0, hi = M;
+    while (hi - lo > 1) {
+      const int64_t mid = lo + (hi - lo) / 2;
+      (need(mid) <= ws_bytes ? lo : hi) = mid;
+    }
+    if (lo == 0) return fail(ARCHEAD_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need(1));
+    if (lo >= kTM) lo -= lo % kTM;
+    const int64_t n = (M + lo - 1) / lo;
+    mc = (M + n - 1) / n;
+    if (lo >= kTM) mc = (mc + kTM - 1) / kTM * kTM;
+  }
+  const WsLayout w = ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, path, M);
   const int64_t row = ldo * (out_dtype == ARCHEAD_F32 ? 4 : 2);
   for (int64_t m0 = 0; m0 < M; m0 += mc) {
     st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, M - m0 < mc ? M - m0 : mc, ldx,
                     static_cast<char*>(out) + m0 * row, out_dtype, ldo, ws, static_cast<hipStream_t>(stream),
-                    path, M);
+                    path, w, m0 == 0);
     if (st != ARCHEAD_OK) return st;
   }
   return ARCHEAD_OK;
@@ -1054,8 +1087,6 @@ archead_status archead_create(const archead_desc* desc, const archead_ptrs* ptrs
   if (strncmp(prop.gcnArchName, "gfx950", 6) != 0)
     return fail(ARCHEAD_E_UNSUPPORTED, "device %d is %s, this library is built for gfx950", dev,
                 prop.gcnArchName);
-  st = scratch_setup(dev);
-  if (st != ARCHEAD_OK) return st;
   archead_handle* h = new (std::nothrow) archead_handle();
   if (!h) return fail(ARCHEAD_E_INVALID_ARG, "out of host memory");
   h->desc = d;
@@ -1077,6 +1108,11 @@ archead_status archead_create(const archead_desc* desc, const archead_ptrs* ptrs
   h->ev_start.store(nullptr);
   h->ev_stop.store(nullptr);
   h->prep.store(nullptr);
+  st = scratch_setup(h);
+  if (st != ARCHEAD_OK) {
+    delete h;
+    return st;
+  }
   *out = h;
   return ARCHEAD_OK;
 }
@@ -1120,8 +1156,9 @@ archead_status archead_logits(const archead_handle* h, const void* x, int64_t M,
   if (st != ARCHEAD_OK || M == 0) return st;
   st = check_out(h, out, out_dtype, ldo);
   if (st != ARCHEAD_OK) return st;
-  return logits_run(h, x, M, ldx, out, out_dtype, ldo, ws, static_cast<hipStream_t>(stream),
-                    choose_path(h, M));
+  const Path path = choose_path(h, M);
+  return logits_run(h, x, M, ldx, out, out_dtype, ldo, ws, static_cast<hipStream_t>(stream), path,
+                    ws_layout_path(h, M, ARCHEAD_OP_LOGITS, path));
 }
 
 archead_status archead_logits_ce(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
@@ -1277,7 +1314,8 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
   for (int64_t m0 = 0; m0 < M; m0 += w.tk_chunk) {
     const int64_t mc = M - m0 < w.tk_chunk ? M - m0 : w.tk_chunk;
     st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, mc, ldx, lg, ARCHEAD_F32, V,
-                    base + w.tk_in_off, s, w.tk_path, M);
+                    base + w.tk_in_off, s, w.tk_path,
+                    ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, w.tk_path, M));
     if (st != ARCHEAD_OK) return st;
     int64_t ldl = V;
     uint32_t* keys = reinterpret_cast<uint32_t*>(base + w.tk_key_off);

@@ -58,14 +58,26 @@ constexpr int kTopKMergeC = 8;            // candidates per thread of that merge
 archead_status fail(archead_status s, const char* fmt, ...);
 void clear_error();
 
-// Device address of the static workspace of archead_logits_noalloc on
-// `device` (the current device), taken once per device; called by
+// Device addresses of the static workspaces of archead_logits_noalloc on the
+// handle's device (the current device), taken once per device; called by
 // archead_create.
-archead_status scratch_setup(int device);
+archead_status scratch_setup(const archead_handle* h);
+// Address of the large one (its own translation unit, so that its memory is
+// there only where a head asks for it) and its size.
+archead_status scratch_large(void** p);
+constexpr size_t kScratchLargeBytes = size_t(272) << 20;
 // Bytes archead_logits_noalloc counts against ARCHEAD_NOALLOC_SCRATCH_BYTES:
-// the workspace of the call (on the tiled kernel's path: its split t, slot
-// biases, per-call tables and split stage-1 partials).
+// the workspace of the call; on the tiled kernel's path the split t, the
+// biases of all scale slots, the head's tables with the factor codes of V_c and
+// B_w as bf16, and the partials of a stage 1 split along d (a count that says
+// which calls are taken; the call itself holds no bf16 factor codes, but a
+// copy of x and its group sums).
 size_t noalloc_bytes(const archead_handle* h, int64_t M);
+// Bytes the call takes in one pass.
+size_t noalloc_call_bytes(const archead_handle* h, int64_t M);
+// Whether an accepted call of the head on the tiled path may take more than
+// `beyond` bytes in one pass.
+bool noalloc_wants(const archead_handle* h, size_t beyond);
 // archead_logits with its checks, in as few chunks of tokens as the workspace
 // allows, on the kernel the whole call would take.
 archead_status logits_in_chunks(const archead_handle* h, const void* x, int64_t M, int64_t ldx, void* out,
