@@ -333,30 +333,39 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
                                    int64_t ldx, int32_t k, float* vals, int64_t* idx,
                                    int64_t ldk, void* ws, size_t ws_bytes, void* stream);
 
-/* Limit of the workspace archead_logits_noalloc counts for a call; its static
- * array, one per device the library runs on (kept until the process ends),
- * holds 4 MiB more for the parts not counted. */
+/* Limit of the bytes archead_logits_noalloc counts for a call (see there). */
 #define ARCHEAD_NOALLOC_SCRATCH_BYTES (4u << 20)
 
 /* archead_logits without a caller workspace, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation.  Same arguments, results and
  * kernels as archead_logits (bit-identical logits), except that the
- * workspace is a static device array inside the library, whose device address archead_create takes once per
- * device.  The call allocates nothing (no hipMalloc, no allocating library
- * routine).
- *   Limit: M whose archead_workspace_bytes(h, M, ARCHEAD_OP_LOGITS), without
- *   the many-token path's copy of x and group sums, exceeds
- *   ARCHEAD_NOALLOC_SCRATCH_BYTES is rejected with ARCHEAD_E_WORKSPACE; where
- *   those do not fit beside the rest, the call runs in chunks of tokens (the
- *   decode-shaped paths fit: at the Qwen3-8B shape, r_c + r_r = 96, every M
- *   up to 32; the many-token path's per-call tables do not).
- *   All calls on one GPU share that GPU's array, which keeps the last call's
+ * workspace is static device memory of the library, whose device address
+ * archead_create takes once per device: an array of 8 MiB, and for heads
+ * with which a call may need more (tables below the limit) one of 272 MiB,
+ * both kept until the process ends.  The call allocates nothing (no
+ * hipMalloc, no allocating library routine).
+ *   Limit: a call whose counted bytes exceed ARCHEAD_NOALLOC_SCRATCH_BYTES is
+ *   rejected with ARCHEAD_E_WORKSPACE.  Counted are, on the decode,
+ *   several-token and GEMV kernels, archead_workspace_bytes(h, M,
+ *   ARCHEAD_OP_LOGITS) (at the Qwen3-8B shape, r_c + r_r = 96, every M up to
+ *   32 fits); on the tiled kernel the sum, each rounded up to 256, of
+ *     128 * M * n_x, n_x = ceil(r_c / 16) + ceil(r_r / 16),
+ *     1024 * ceil(M / 256) * (d/g + (r_c > 0) + (r_r > 0)),
+ *     archead_prepared_bytes(h),
+ *     2 * (r_c + r_r) * d, and
+ *     4 * s * M * (r_c + r_r) where s > 1: s starts at 1 and doubles while
+ *     ceil(M / 16) * ceil((r_c + r_r) / 64) * s < 256, d/g is a multiple of
+ *     2 s and d/g / (2 s) >= 8 (r_c + r_r = 0: s = 1).
+ *   The static memory holds every accepted call of groups up to 128 in one
+ *   pass; of larger groups, calls whose copy of x (2 * M * d bytes) does not
+ *   fit run in several chunks of tokens.
+ *   All calls on one GPU share that GPU's memory, which keeps the last call's
  *   contents (no call needs it cleared): calls that overlap on one GPU, on
  *   different streams or from different threads, race and give undefined
  *   results; serialise them.
- * Errors as archead_logits, plus ARCHEAD_E_HIP when the array's address
- * could not be taken at create time. */
+ * Errors as archead_logits.  ARCHEAD_E_HIP from archead_create when an
+ * address could not be taken. */
 archead_status archead_logits_noalloc(const archead_handle* h, const void* x, int64_t M,
                                       int64_t ldx, void* out, archead_dtype out_dtype,
                                       int64_t ldo, void* stream);

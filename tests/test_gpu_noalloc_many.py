@@ -83,3 +83,46 @@ def test_chunks_of_a_copy_beyond_the_static_memory(prepared):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     finally:
         ph.close()
+
+
+def _counted(ph, M, V, d, g, rc, rr):
+    """The bytes the header says a call of the tiled path is counted with."""
+    up = lambda n: (n + 255) // 256 * 256
+    n_x = (rc + 15) // 16 + (rr + 15) // 16
+    n = up(128 * M * n_x) + up(1024 * ((M + 255) // 256) * (d // g + (rc > 0) + (rr > 0)))
+    n += ph.prepared_bytes() + up(2 * (rc + rr) * d)
+    s, blocks = 1, ((M + 15) // 16) * ((rc + rr + 63) // 64)
+    while rc + rr and blocks * s < 256 and (d // g) % (2 * s) == 0 and d // g // (2 * s) >= 8:
+        s *= 2
+    return n + (up(4 * s * M * (rc + rr)) if s > 1 else 0)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(V=77, d=512, g=64, rc=16, rr=4),
+    dict(V=500, d=1024, g=128, rc=0, rr=0),
+    dict(V=3000, d=2048, g=64, rc=64, rr=32),    # (stage 1 split along d)
+    dict(V=12000, d=512, g=64, rc=64, rr=32),    # tables close to the limit
+])
+def test_limit_is_the_documented_one(kw):
+    from paper_2608_02703_amd import PackedHead, archead as ab
+    ph = PackedHead.from_arrays(make_head("tiny", **kw))
+    ph.force_path("tiled")
+    try:
+        count = lambda M: _counted(ph, M, **kw)
+        lo, hi = 0, 1 << 20
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if count(mid) <= ab.NOALLOC_SCRATCH_BYTES else (lo, mid)
+        for M in sorted({1, lo - 1, lo, lo + 1, lo + 257} & set(range(1, 1 << 20))):
+            say(f"noalloc limit {kw} M={M}")
+            x = torch.zeros((M, kw["d"]), dtype=torch.bfloat16, device="cuda")
+            out = torch.empty((M, kw["V"]), device="cuda", dtype=torch.bfloat16)
+            if count(M) <= ab.NOALLOC_SCRATCH_BYTES:
+                ph.logits_noalloc(x, out=out)
+            else:
+                with pytest.raises(ab.ArcheadError) as e:
+                    ph.logits_noalloc(x, out=out)
+                assert e.value.status == ab.E_WORKSPACE
+        torch.cuda.synchronize()
+    finally:
+        ph.close()
