@@ -653,15 +653,24 @@ GemvArgs gemv_args(const archead_handle* h, const void* x, int64_t ldx, uint64_t
   return a;
 }
 
+// Which part of a call's tokens a launch serves (a call in chunks).
+struct Part { bool first = true, last = true; };
+
+// The timing events (if set) are attached to the call's first and last
+// dispatch packets themselves, so they bracket exactly the kernel execution.
+struct Timing { hipEvent_t start, stop; };
+Timing timing_events(const archead_handle* h, Part part) {
+  return {part.first ? static_cast<hipEvent_t>(h->ev_start.load(std::memory_order_relaxed)) : nullptr,
+          part.last ? static_cast<hipEvent_t>(h->ev_stop.load(std::memory_order_relaxed)) : nullptr};
+}
+
 // One launch per group of up to 4 tokens.  forced_grid > 0 fixes the grid
 // (the CE passes, whose partials are indexed by workgroup).
 archead_status launch_gemv_passes(const archead_handle* h, GemvArgs a, int64_t M, bool ce,
-                                  int64_t forced_grid, hipStream_t s, bool topk = false) {
+                                  int64_t forced_grid, hipStream_t s, bool topk = false,
+                                  Part part = {}) {
   const int lpr = lanes_per_row(h->desc);
-  // timing events (if set) are attached to the first and last dispatch
-  // packets themselves, so they bracket exactly the kernel execution
-  hipEvent_t ev0 = static_cast<hipEvent_t>(h->ev_start.load(std::memory_order_relaxed));
-  hipEvent_t ev1 = static_cast<hipEvent_t>(h->ev_stop.load(std::memory_order_relaxed));
+  const Timing ev = timing_events(h, part);
   for (int64_t m0 = 0; m0 < M; m0 += 4) {
     const int tok = int(M - m0 < 4 ? M - m0 : 4);
     const bool sc8 = h->desc.scale_dtype == ARCHEAD_U8;
@@ -677,8 +686,8 @@ archead_status launch_gemv_passes(const archead_handle* h, GemvArgs a, int64_t M
     void* args[] = {&a};
     const bool first = m0 == 0, last = m0 + 4 >= M;
     hipError_t e = hipExtLaunchKernel(fn, dim3(unsigned(grid)),
-                                      dim3(kBlock), args, lds, s, first ? ev0 : nullptr,
-                                      last ? ev1 : nullptr, 0);
+                                      dim3(kBlock), args, lds, s, first ? ev.start : nullptr,
+                                      last ? ev.stop : nullptr, 0);
     if (e != hipSuccess) return hip_fail(e, "GEMV launch");
   }
   return ARCHEAD_OK;
@@ -687,7 +696,7 @@ archead_status launch_gemv_passes(const archead_handle* h, GemvArgs a, int64_t M
 // One launch per pass of up to dec_tokens_per_pass tokens.  The CE form
 // writes one softmax partial per consumer workgroup.
 archead_status launch_dec(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
-                          uint64_t* tst, DecArgs a, bool ce, hipStream_t s) {
+                          uint64_t* tst, DecArgs a, bool ce, hipStream_t s, Part part = {}) {
   const archead_desc& d = h->desc;
   const DecGrid gr = dec_grid(h);
   const int tpp = dec_tokens_per_pass(d);
@@ -713,8 +722,7 @@ archead_status launch_dec(const archead_handle* h, const void* x, int64_t M, int
   a.cu_row = int(core_u_row_bytes(d));
   a.u5 = d.core_u_dtype == ARCHEAD_I5;
   a.rrs = sc8 ? static_cast<const uint16_t*>(h->ptrs.res_row_scales) : a.rs;
-  hipEvent_t ev0 = static_cast<hipEvent_t>(h->ev_start.load(std::memory_order_relaxed));
-  hipEvent_t ev1 = static_cast<hipEvent_t>(h->ev_stop.load(std::memory_order_relaxed));
+  const Timing ev = timing_events(h, part);
   const int64_t grid = gr.prod_blocks + gr.consumer_blocks;
   for (int64_t m0 = 0; m0 < M; m0 += tpp) {
     const int tok = int(M - m0 < tpp ? M - m0 : tpp);
@@ -732,7 +740,7 @@ archead_status launch_dec(const archead_handle* h, const void* x, int64_t M, int
     const bool first = m0 == 0, last = m0 + tpp >= M;
     hipError_t e = hipExtLaunchKernel(fn, dim3(unsigned(grid)),
                                       dim3(kDBlock), args, size_t(l.total), s,
-                                      first ? ev0 : nullptr, last ? ev1 : nullptr, 0);
+                                      first ? ev.start : nullptr, last ? ev.stop : nullptr, 0);
     if (e != hipSuccess) return hip_fail(e, "MFMA decode launch");
   }
   return ARCHEAD_OK;
@@ -741,7 +749,7 @@ archead_status launch_dec(const archead_handle* h, const void* x, int64_t M, int
 // One launch per tile of up to 32 tokens.  The CE form writes one softmax
 // partial per consumer workgroup.
 archead_status launch_mid(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
-                          uint64_t* tst, MidArgs a, bool ce, hipStream_t s) {
+                          uint64_t* tst, MidArgs a, bool ce, hipStream_t s, Part part = {}) {
   const archead_desc& d = h->desc;
   const MidGrid gr = mid_grid(h);
   a.codes = static_cast<const uint8_t*>(h->ptrs.res_codes);
@@ -763,8 +771,7 @@ archead_status launch_mid(const archead_handle* h, const void* x, int64_t M, int
   a.n_cblocks = int(gr.cblocks);
   a.n_prod_blocks = gr.prod_blocks;
   const int gw = int(d.g / 32);
-  hipEvent_t ev0 = static_cast<hipEvent_t>(h->ev_start.load(std::memory_order_relaxed));
-  hipEvent_t ev1 = static_cast<hipEvent_t>(h->ev_stop.load(std::memory_order_relaxed));
+  const Timing ev = timing_events(h, part);
   const int64_t grid = gr.prod_blocks + gr.cblocks;
   for (int64_t m0 = 0; m0 < M; m0 += kMidTokMax) {
     const int tok = int(M - m0 < kMidTokMax ? M - m0 : kMidTokMax);
@@ -785,7 +792,7 @@ archead_status launch_mid(const archead_handle* h, const void* x, int64_t M, int
     const bool first = m0 == 0, last = m0 + kMidTokMax >= M;
     hipError_t e = hipExtLaunchKernel(fn, dim3(unsigned(grid)),
                                       dim3(kMidBlock), args, size_t(l.total), s,
-                                      first ? ev0 : nullptr, last ? ev1 : nullptr, 0);
+                                      first ? ev.start : nullptr, last ? ev.stop : nullptr, 0);
     if (e != hipSuccess) return hip_fail(e, "several-token launch");
   }
   return ARCHEAD_OK;
@@ -858,20 +865,19 @@ MfmaArgs mfma_args(const archead_handle* h, int64_t M, const WsLayout& w, char* 
   return a;
 }
 
-archead_status launch_mfma(const archead_handle* h, MfmaArgs& a, bool ce, hipStream_t s) {
+archead_status launch_mfma(const archead_handle* h, MfmaArgs& a, bool ce, hipStream_t s, Part part = {}) {
   const TiledShape ts = tiled_shape(h, a.M);
   const void* fn = kern::mfma(ce, ts.tm, ts.nw);
   const int lds = ts.nw == 4 ? (ts.tm == 64 ? MGeomT<64, 4>::LDS : MGeomT<128, 4>::LDS)
                   : ts.tm == 128 ? MGeomT<128>::LDS : MGeom::LDS;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return hip_fail(e, "MFMA LDS size attribute");
-  hipEvent_t ev0 = static_cast<hipEvent_t>(h->ev_start.load(std::memory_order_relaxed));
-  hipEvent_t ev1 = static_cast<hipEvent_t>(h->ev_stop.load(std::memory_order_relaxed));
+  const Timing ev = timing_events(h, part);
   void* args[] = {&a};
   const int64_t grid = 8 * a.tiles_per_xcd;
   if (grid > 0x7fffffff) return fail(ARCHEAD_E_UNSUPPORTED, "too many MFMA tiles");
   e = hipExtLaunchKernel(fn, dim3(unsigned(grid)), dim3(unsigned(ts.nw * 64)), args, size_t(lds), s,
-                         ev0, ev1, 0);
+                         ev.start, ev.stop, 0);
   return e == hipSuccess ? ARCHEAD_OK : hip_fail(e, "MFMA launch");
 }
 
@@ -934,7 +940,7 @@ archead_status launch_softmax_partials(const archead_handle* h, const void* x, i
 // launch_mfma_prologue.
 archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int64_t ldx,
                           void* out, archead_dtype out_dtype, int64_t ldo, void* ws,
-                          hipStream_t s, Path path, const WsLayout& w, bool tables = true) {
+                          hipStream_t s, Path path, const WsLayout& w, Part part = {}, bool tables = true) {
   archead_status st = ARCHEAD_OK;
   if (path == Path::kDec) {
     DecArgs a;
@@ -944,7 +950,7 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
     a.out_bf16 = out_dtype == ARCHEAD_BF16;
     return launch_dec(h, x, M, ldx,
                       reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + w.tst_off), a, false,
-                      s);
+                      s, part);
   }
   if (path == Path::kMid) {
     MidArgs a;
@@ -954,7 +960,7 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
     a.out_bf16 = out_dtype == ARCHEAD_BF16;
     return launch_mid(h, x, M, ldx,
                       reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + w.tst_off), a, false,
-                      s);
+                      s, part);
   }
   if (path == Path::kTiled) {
     st = launch_mfma_prologue(h, x, M, ldx, w, static_cast<char*>(ws), s, false, tables);
@@ -963,13 +969,13 @@ archead_status logits_run(const archead_handle* h, const void* x, int64_t M, int
     a.out = out;
     a.ldo = ldo;
     a.out_bf16 = out_dtype == ARCHEAD_BF16;
-    return launch_mfma(h, a, false, s);
+    return launch_mfma(h, a, false, s, part);
   }
   GemvArgs a = gemv_args(h, x, ldx, reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + w.tst_off));
   a.out = out;
   a.ldo = ldo;
   a.out_bf16 = out_dtype == ARCHEAD_BF16;
-  return launch_gemv_passes(h, a, M, false, 0, s);
+  return launch_gemv_passes(h, a, M, false, 0, s, false, part);
 }
 
 
@@ -1038,7 +1044,7 @@ archead_status logits_in_chunks(const archead_handle* h, const void* x, int64_t 
   for (int64_t m0 = 0; m0 < M; m0 += mc) {
     st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, M - m0 < mc ? M - m0 : mc, ldx,
                     static_cast<char*>(out) + m0 * row, out_dtype, ldo, ws, static_cast<hipStream_t>(stream),
-                    path, w, m0 == 0);
+                    path, w, Part{m0 == 0, m0 + mc >= M}, m0 == 0);
     if (st != ARCHEAD_OK) return st;
   }
   return ARCHEAD_OK;
@@ -1315,7 +1321,7 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
     const int64_t mc = M - m0 < w.tk_chunk ? M - m0 : w.tk_chunk;
     st = logits_run(h, static_cast<const uint16_t*>(x) + m0 * ldx, mc, ldx, lg, ARCHEAD_F32, V,
                     base + w.tk_in_off, s, w.tk_path,
-                    ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, w.tk_path, M));
+                    ws_layout_path(h, mc, ARCHEAD_OP_LOGITS, w.tk_path, M), Part{m0 == 0, m0 + mc >= M});
     if (st != ARCHEAD_OK) return st;
     int64_t ldl = V;
     uint32_t* keys = reinterpret_cast<uint32_t*>(base + w.tk_key_off);
