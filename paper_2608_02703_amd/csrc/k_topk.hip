@@ -88,10 +88,15 @@ __device__ __forceinline__ void tk_row16_best(float& v, int& i) {
 // (as an order key); the k-th largest of a row's chunk maxima is a floor for
 // its k-th largest logit, so k_topk_select reads again only the chunks whose
 // maximum reaches the floor (k of them, but for ties) and ranks the few logits
-// at or above it.  What bounds it: the first launch reads the logits once, from
+// at or above it.  Of chunks whose maxima are equal it reads no more than can be
+// wanted, and a row with many logits at or above the floor (few chunks, equal or
+// sorted logits) is reduced to its k best by counting first, so no values make
+// it slow.  What bounds it: the first launch reads the logits once, from
 // the caches for the usual sizes; the second is a chain of short steps of one
 // workgroup per token.  24 tokens of 128256 logits, k = 50: 5.5 + 9.3 us
-// (sorted lists per slice and a merge in k rounds: 61 + 52 us).
+// (sorted lists per slice and a merge in k rounds: 61 + 52 us).  24 tokens of
+// 151936 logits, k = 10 / 50, both: random 17 / 20 us, around 1000 18 / 21, all
+// equal 28 / 44, ascending 28 / 49.
 //
 // Order key of a logit: larger for larger values, equal for equal ones (0 and
 // -0), 0 for NaN (which is never selected).
@@ -102,7 +107,9 @@ __device__ __forceinline__ uint32_t tk_key(float v) {
 
 constexpr int kChunkUnit = 64;           // logits a wave takes per load
 constexpr int kSelBlock = 1024, kSelWaves = kSelBlock / 64;
-constexpr int kSelCand = 4096;           // candidates held; more take the list scan
+constexpr int kSelCand = 128;            // candidates ranked one against all; more are reduced to k first
+constexpr int kRedFew = 4, kRedMany = 16;   // units a wave of that reduction holds
+static_assert(kSelCand >= kTopKMax, "room for the k best");
 constexpr int kWaveUnits = 16;           // units a wave of k_topk_max takes at a time
 constexpr int kSelUnits = 8;             // units a wave of k_topk_select has in flight
 static_assert(archead::kTopKChunks == kSelBlock && archead::kTopKChunkUnit == kChunkUnit &&
@@ -149,10 +156,10 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
   __shared__ int slist[kSelBlock];
   __shared__ float cval[kSelCand];
   __shared__ int cidx[kSelCand];
-  __shared__ float ov[kTopKMax];
-  __shared__ int oi[kTopKMax];
+  __shared__ int sties[kSelWaves];   // chunks at the floor before each wave's
+  __shared__ int scount[2][64];
   __shared__ uint32_t sfloor;
-  __shared__ int nlist, ncand;
+  __shared__ int smost, nlist, ncand;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t m = blockIdx.x;
@@ -165,33 +172,66 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
   }
   __syncthreads();
   if (wid == 0) {
-    // the largest key prefix of 20 bits that at least k chunk maxima reach
-    // (the low bits only decide how many more chunks are read)
+    // the largest key prefix that at least k chunk maxima reach: of 20 bits,
+    // and where clearly more than k reach that one (a large common offset,
+    // ties) of up to 32, the k-th largest maximum itself
     uint32_t kk[kSelWaves];
 #pragma unroll
     for (int i = 0; i < kSelWaves; ++i) kk[i] = skey[64 * i + lane];
+    const int enough = k + k / 4 + 3;   // (reading a few chunks more is cheaper than 12 steps more)
     uint32_t f = 0;
-    for (int bit = 31; bit >= 12; --bit) {
+    int reach = n_chunk;   // maxima that reach f
+    for (int bit = n_chunk < k ? -1 : 31; bit >= 12 || (bit >= 0 && reach > enough); --bit) {
       const uint32_t t = f | (1u << bit);
       int n = 0;
 #pragma unroll
       for (int i = 0; i < kSelWaves; ++i) n += __popcll(__ballot(kk[i] >= t));
-      if (n >= k) f = t;
+      if (n >= k) {
+        f = t;
+        reach = n;
+      }
     }
-    if (lane == 0) sfloor = f ? f : 1u;   // 1: every logit but NaN
+    int most = kSelBlock;
+    if (f && reach > enough) {
+      // Many maxima equal to f: the first k - (maxima above f) of their chunks
+      // hold as many of the logits equal to f as can be wanted, those of the
+      // smallest indices among them; no other chunk of f's is read.
+      int before = 0;
+      most = k;
+#pragma unroll
+      for (int i = 0; i < kSelWaves; ++i) {
+        if (lane == 0) sties[i] = before;
+        before += __popcll(__ballot(kk[i] == f));
+        most -= __popcll(__ballot(kk[i] > f));
+      }
+    }
+    if (lane == 0) {
+      sfloor = f ? f : 1u;   // 1: every logit but NaN
+      smost = most;
+    }
   }
   __syncthreads();
   const uint32_t fl = sfloor;
-  if (mine >= fl) slist[atomicAdd(&nlist, 1)] = tid;
+  const uint64_t lower = (uint64_t(1) << lane) - 1;
+  bool listed = mine >= fl;
+  if (smost < kSelBlock) {
+    const uint64_t tie = __ballot(mine == fl);
+    listed = mine > fl || (mine == fl && sties[wid] + __popcll(tie & lower) < smost);
+  }
+  if (listed) slist[atomicAdd(&nlist, 1)] = tid;
   __syncthreads();
   const int lu = __builtin_ctz(cs / kChunkUnit), units = nlist << lu;   // (a power of two)
+  // this lane's logit of unit u of the listed chunks: its index (V: none)
+  auto index_of = [&](int u) {
+    const int64_t j = u < units ? int64_t(slist[u >> lu]) * cs + (u & ((1 << lu) - 1)) * kChunkUnit + lane : V;
+    return int(j < V ? j : V);
+  };
   for (int u0 = wid; u0 < units; u0 += kSelUnits * kSelWaves) {
     float v[kSelUnits];
-    int64_t j[kSelUnits];
+    int j[kSelUnits];
 #pragma unroll
     for (int b = 0; b < kSelUnits; ++b) {
-      const int u = u0 + b * kSelWaves;
-      j[b] = u < units ? int64_t(slist[u >> lu]) * cs + (u & ((1 << lu) - 1)) * kChunkUnit + lane : V;
+      j[b] = index_of(u0 + b * kSelWaves);
       v[b] = j[b] < V ? row[j[b]] : NAN;
     }
 #pragma unroll
@@ -201,28 +241,97 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
       if (!mask) continue;
       int at = 0;
       if (lane == 0) at = atomicAdd(&ncand, __popcll(mask));
-      at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((uint64_t(1) << lane) - 1));
+      at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & lower);
       if (hit && at < kSelCand) {
         cval[at] = v[b];
-        cidx[at] = int(j[b]);
+        cidx[at] = j[b];
       }
     }
   }
   __syncthreads();
-  const int nc = ncand;
+  int nc = ncand;
   if (nc > kSelCand) {
-    // (many logits tied at the floor) sorted lists over the whole row, one per
-    // wave, merged by rank
-    float lv = -INFINITY, bv = -INFINITY;
-    int li = kNoIdx, bi = kNoIdx;
-    for (int64_t j = tid; j - lane < V; j += kSelBlock)
-      tk_offer(lv, li, bv, bi, j < V ? row[j] : NAN, int(j), j < V, lane, k);
-    tk_rank_merge<kSelWaves>(lv, li, tid, k, cval, cidx, ov, oi);
-    if (tid < k) {
-      if (vals) vals[m * ldk + tid] = ov[tid];
-      idx[m * ldk + tid] = oi[tid] == kNoIdx ? int64_t(-1) : int64_t(oi[tid]);
-    }
-    return;
+    // More than are ranked one against all: the k best of them, some units
+    // a wave at a time together with the k best so far, by a search for the
+    // k-th largest key and among its equals for the largest index taken; the
+    // whole workgroup counts.  Its cost depends on the number of logits alone.
+    uint32_t top = mine;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) top = max(top, uint32_t(__shfl_xor(int(top), off, 64)));
+    if (lane == 0) skey[wid] = top;   // (its words were read above)
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) top = max(top, skey[w]);
+    const int high = top == fl ? -1 : 31 - __builtin_clz(top ^ fl);   // the keys agree above it
+    int have = 0, end = int(V);
+    uint32_t f = fl;
+    auto reduce = [&](auto units_per_wave) {
+      constexpr int kRedUnits = decltype(units_per_wave)::value;
+      for (int r0 = 0; r0 < units; r0 += kRedUnits * kSelWaves) {
+        // element 0: one of the k best so far; then this round's that may join them
+        uint32_t key[kRedUnits + 1];
+        int j[kRedUnits + 1];
+        j[0] = tid < have ? cidx[tid] : int(V);
+        key[0] = tid < have ? tk_key(cval[tid]) : 0u;
+#pragma unroll
+        for (int b = 1; b <= kRedUnits; ++b) {
+          j[b] = index_of(r0 + wid + (b - 1) * kSelWaves);
+          key[b] = j[b] < V ? tk_key(row[j[b]]) : 0u;
+          if (!(key[b] > f || (key[b] == f && j[b] < end))) key[b] = 0u;
+        }
+        __syncthreads();   // every thread has read ncand, the counts and the k best so far
+        if (tid < 64) scount[0][tid] = scount[1][tid] = 0;
+        if (tid == 0) ncand = 0;
+        __syncthreads();
+        // Logits of the workgroup that satisfy `hit`; each word of scount once.
+        auto count = [&](int* word, auto hit) {
+          int n = 0;
+#pragma unroll
+          for (int b = 0; b <= kRedUnits; ++b) n += __popcll(__ballot(hit(key[b], j[b])));
+          if (lane == 0 && n) atomicAdd(word, n);
+          __syncthreads();
+          return *word;
+        };
+        const int n_in = count(&scount[0][32], [&](uint32_t kb, int) { return kb > 0; });
+        if (n_in == have) continue;
+        end = int(V);   // equals of f from this index on are left out
+        if (n_in > k) {
+          f = high == 31 ? 0u : fl >> (high + 1) << (high + 1);
+          int reach = n_in;
+          for (int bit = high; bit >= 0 && reach != k; --bit) {
+            const uint32_t t = f | (1u << bit);
+            const int n = count(&scount[0][bit], [&](uint32_t kb, int) { return kb >= t; });
+            if (n >= k) {
+              f = t;
+              reach = n;
+            }
+          }
+          if (reach != k) {
+            const int want = k - count(&scount[0][33], [&](uint32_t kb, int) { return kb > f; });
+            int n = -1;
+            end = 0;
+            for (int bit = 31 - __builtin_clz(int(V)); bit >= 0 && n != want; --bit) {
+              const int t = end | (1 << bit);
+              n = count(&scount[1][bit], [&](uint32_t kb, int jb) { return kb == f && jb < t; });
+              if (n <= want) end = t;
+            }
+          }
+        }
+#pragma unroll
+        for (int b = 0; b <= kRedUnits; ++b) {
+          if (key[b] > f || (key[b] == f && j[b] < end)) {
+            const int at = atomicAdd(&ncand, 1);
+            cval[at] = row[j[b]];
+            cidx[at] = j[b];
+          }
+        }
+        __syncthreads();
+        have = ncand;
+      }
+    };
+    if (units <= kRedFew * kSelWaves) reduce(std::integral_constant<int, kRedFew>{});
+    else reduce(std::integral_constant<int, kRedMany>{});
+    nc = have;
   }
   // rank each candidate among all (distinct indices: distinct ranks)
   for (int t = tid; t < nc; t += kSelBlock) {

@@ -226,3 +226,67 @@ def test_topk_of_chunks_selects_over_the_whole_calls_logits(M, d):
         _check(ph, make_x("tiny", M, d=d), 10, what=f"chunks M={M}")
     finally:
         ph.close()
+
+
+def _row_kinds(V):
+    """Heads (d = g = 64, a core and a correction of rank 1) whose logits over
+    the vocabulary are of one kind, and whether x is (1, 0, ..., 0) instead of
+    ones with noise."""
+    v = np.arange(V)
+    for kind, order in (("random", None), ("offset", None), ("ascending", v), ("descending", v[::-1]),
+                        ("equal", 0 * v)):
+        h = make_head("tiny", V=V, d=64, g=64, rc=1, rr=1)
+        if order is None:          # +- 0.25, around 0 or around 1000
+            h.res_scales[:] = 0.0017
+            h.core_u[:] = h.core_v[:] = 1
+            h.core_v_scale[:] = 1
+            h.core_u_scale[:] = 1000 / 64 if kind == "offset" else 0
+            h.corr_a[:] = 0
+        else:                      # multiples of 2^-10: the whole part, then the rest
+            h.res_codes[:] = 0x88
+            h.res_codes[:, 0] = 0x89
+            h.res_scales[:, 0] = order // 1024
+            h.core_u[:] = 0
+            h.corr_a[:] = 1
+            h.corr_a_scale[:] = order % 1024 / 1024
+            h.corr_b[:] = 0
+            h.corr_b[0, 0] = 1
+            h.corr_b_scale[:] = 1
+        yield kind, h, order is not None
+
+
+@pytest.mark.parametrize("V", [4000, 151936])
+def test_topk_time_hardly_depends_on_the_values(V):
+    """Rows around a large value, sorted ones and rows of equal logits (a padding
+    token's) are selected from in about the time of random ones: within a
+    factor of two over the whole call.  (Reading every chunk that ties at the
+    floor and ranking thousands of logits one against all took 4 times as long
+    for rows around 1000 and 20 to 50 times for sorted ones.)"""
+    from paper_2608_02703_amd import PackedHead
+    M, us = 24, {}
+    for kind, h, first in _row_kinds(V):
+        ph = PackedHead.from_arrays(h)
+        try:
+            x = torch.ones((M, 64), device="cuda")
+            if first:
+                x[:, 1:] = 0
+            else:
+                x += 0.1 * torch.randn((M, 64), generator=torch.Generator().manual_seed(1)).cuda()
+            x = x.bfloat16()
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            for k in (10, 50, 64):
+                say(f"top-k of {kind} rows V={V} k={k}")
+                _check(ph, x.view(torch.int16).cpu().numpy().view(np.uint16), k, what=kind)
+                best = float("inf")
+                for _ in range(5):
+                    e[0].record()
+                    for _ in range(10):
+                        ph.logits_topk(x, k)
+                    e[1].record()
+                    e[1].synchronize()
+                    best = min(best, e[0].elapsed_time(e[1]) * 100)
+                us[kind, k] = best
+                say(f"  {best:.1f} us")
+                assert best <= 2 * us["random", k]
+        finally:
+            ph.close()
