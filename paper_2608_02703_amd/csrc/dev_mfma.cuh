@@ -92,6 +92,14 @@ struct FidTilePart {
 constexpr int kNoCol = 0x7fff;
 static_assert(sizeof(FidTilePart) == 32, "the workspace holds 32 bytes per tile and token");
 
+// f(LO) + .. + f(LO + N - 1) as a tree (f takes an integral_constant): log2 N
+// roundings in a lane's sums over a tile, where one after the other makes N.
+template <int LO, int N, typename F>
+__device__ __forceinline__ auto tree_sum(F f) {
+  if constexpr (N == 1) return f(std::integral_constant<int, LO>{});
+  else return tree_sum<LO, N / 2>(f) + tree_sum<LO + N / 2, N / 2>(f);
+}
+
 // XE: 0 logits or CE (CE), 1 the fidelity pass (the dense head's rows are
 // loaded straight into the waves' registers, one stage ahead, and accumulated
 // beside the packed logits; per-tile FidTilePart out), 2 the rank pass (per
@@ -530,19 +538,35 @@ void k_mfma(MfmaArgs a) {
       const int oib = __shfl_xor(ib, 32, 64);
       ib = omb > mb ? oib : (omb == mb ? min(ib, oib) : ib);
       mb = fmaxf(mb, omb);
+      // in groups of 4, of 16 and of all 32: 7 roundings (the tree of
+      // tree_sum spills here)
       float sa = 0.f, sb = 0.f, t = 0.f, sq = 0.f;
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
+      for (int ni = 0; ni < NI; ++ni) {
+        float na = 0.f, nb = 0.f, nt = 0.f, nq = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          if (partial && col_of(ni, i) >= cols) continue;
-          const float av = accd[mi][ni][i], bv = acc[mi][ni][i];
-          const float ea = expf(av - ma), dd = av - bv;
-          sa += ea;
-          sb += expf(bv - mb);
-          t += ea * dd;
-          sq += dd * dd;
+        for (int k = 0; k < 16; k += 4) {
+          float ga = 0.f, gb = 0.f, gt = 0.f, gq = 0.f;
+#pragma unroll
+          for (int i = k; i < k + 4; ++i) {
+            if (partial && col_of(ni, i) >= cols) continue;
+            const float av = accd[mi][ni][i], bv = acc[mi][ni][i];
+            const float ea = expf(av - ma), dd = av - bv;
+            ga += ea;
+            gb += expf(bv - mb);
+            gt += ea * dd;
+            gq += dd * dd;
+          }
+          na += ga;
+          nb += gb;
+          nt += gt;
+          nq += gq;
         }
+        sa += na;
+        sb += nb;
+        t += nt;
+        sq += nq;
+      }
       sa += __shfl_xor(sa, 32, 64);
       sb += __shfl_xor(sb, 32, 64);
       t += __shfl_xor(t, 32, 64);
@@ -692,15 +716,17 @@ void k_mfma(MfmaArgs a) {
           for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[mi][ni][i]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float ref = mx == -INFINITY ? 0.f : mx;   // no valid column: a sum of zeros
-        float se = 0.f;
+        float se = tree_sum<0, 16 * NI>([&](auto c) {
+          return fast_exp(acc[mi][decltype(c)::value / 16][decltype(c)::value % 16] - ref);
+        });
         int ai = kNoIdx;
+        if constexpr (kIdx) {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+          for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            se += fast_exp(acc[mi][ni][i] - ref);
-            if (kIdx && acc[mi][ni][i] == mx && col_of(ni, i) < cols) ai = min(ai, col_of(ni, i));
-          }
+            for (int i = 0; i < 16; ++i)
+              if (acc[mi][ni][i] == mx && col_of(ni, i) < cols) ai = min(ai, col_of(ni, i));
+        }
         se += __shfl_xor(se, 32, 64);
         if constexpr (kIdx) ai = min(ai, __shfl_xor(ai, 32, 64));
         if (h == 0) {
