@@ -294,26 +294,21 @@ PrepLayout prep_layout(const archead_handle* h) {
   return p;
 }
 
-// Whether a top-k call of M tokens runs fused in the single-token GEMV.
-// The merge of per-partial top-k lists: k rounds of a workgroup-wide best
-// when every thread holds at most kTopKMergeC candidates, else the scan
-// (floor, per-wave lists, wave-ordered merge).
-static hipError_t launch_topk_merge(int64_t n_part, int k, int64_t rows, void** args,
-                                    hipStream_t s) {
-  // four waves while they hold every candidate (a round's barrier and
-  // cross-wave step are cheaper), else sixteen
-  if (n_part * k <= int64_t(256) * kTopKMergeC)
-    return hipLaunchKernel(kern::topk_merge(256), dim3(unsigned(rows)), dim3(256), args, 0, s);
-  if (n_part * k <= int64_t(kTopKMergeBlock) * kTopKMergeC)
-    return hipLaunchKernel(kern::topk_merge(kTopKMergeBlock), dim3(unsigned(rows)),
-                           dim3(kTopKMergeBlock), args, 0, s);
-  return hipLaunchKernel(kern::topk_merge_scan(), dim3(unsigned(rows)), dim3(kBlock), args, 0, s);
+// The merge of the fused form's lists, k rounds of a workgroup-wide best, by
+// four waves while they hold every candidate (a round's barrier and cross-wave
+// step are cheaper), else by sixteen, which hold those of every grid that
+// topk_fused accepts.
+static hipError_t launch_topk_merge(int64_t n_part, int k, void** args, hipStream_t s) {
+  const int block = n_part * k <= int64_t(256) * kTopKMergeC ? 256 : kTopKMergeBlock;
+  return hipLaunchKernel(kern::topk_merge(block), dim3(1), dim3(unsigned(block)), args, 0, s);
 }
 
+// Whether a top-k call of M tokens may run fused in the single-token GEMV.
 bool topk_fused(const archead_handle* h, int64_t M) {
   return M == 1 && choose_path(h, 1) == Path::kGemv &&
          kern::gemv_topk(lanes_per_row(h->desc), h->desc.scale_dtype == ARCHEAD_U8,
-                         gemv_mode(h).gen) != nullptr;
+                         gemv_mode(h).gen) != nullptr &&
+         gemv_grid(h, 1, false, true) * kTopKFusedK <= int64_t(kTopKMergeBlock) * kTopKMergeC;
 }
 
 // One token may take either form (by k, which the layout does not know): both
@@ -327,7 +322,7 @@ static WsLayout topk_layout(const archead_handle* h, int64_t M) {
     off = w.total;
     w.tk_fused = true;
     w.n_part = gemv_grid(h, 1, false, true);
-    const size_t lists = size_t(w.n_part) * kTopKMaxK;
+    const size_t lists = size_t(w.n_part) * kTopKFusedK;
     w.tk_pv_off = off;
     off = align256(off + sizeof(float) * lists);
     w.tk_pi_off = off;
@@ -1312,7 +1307,7 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
     st = launch_gemv_passes(h, a, 1, false, np, s, true);
     if (st != ARCHEAD_OK) return st;
     void* margs[] = {&pv, &pi, &np, &k, &vals, &idx, &ldk};
-    e = launch_topk_merge(np, k, 1, margs, s);
+    e = launch_topk_merge(np, k, margs, s);
     return e == hipSuccess ? ARCHEAD_OK : hip_fail(e, "top-k merge launch");
   }
   const int64_t V = h->desc.V;

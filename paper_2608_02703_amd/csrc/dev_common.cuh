@@ -640,26 +640,4 @@ __device__ __forceinline__ void tk_rank_merge(float lv, int li, int tid, int k, 
   __syncthreads();
 }
 
-// Merge the lists of a workgroup's NW waves into wave 0's (the other waves'
-// lists are inserted in wave order; each is sorted, so its first entry
-// that fails the bar ends it).  sv / si: LDS of NW * 64 entries.  Contains
-// a barrier: every wave of the workgroup calls it.
-template <int NW>
-__device__ __forceinline__ void tk_block_merge(float& lv, int& li, float& bv, int& bi, int lane,
-                                               int wid, int k, float* sv, int* si) {
-  sv[wid * 64 + lane] = lv;
-  si[wid * 64 + lane] = li;
-  __syncthreads();
-  if (wid == 0) {
-    for (int w = 1; w < NW; ++w)
-      for (int j = 0; j < k; ++j) {
-        const float cv = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(sv[w * 64 + j])));
-        const int ci = __builtin_amdgcn_readfirstlane(si[w * 64 + j]);
-        if (!tk_better(cv, ci, bv, bi)) break;
-        tk_insert(lv, li, bv, bi, cv, ci, lane, k);
-      }
-  }
-}
-
-
 }  // namespace

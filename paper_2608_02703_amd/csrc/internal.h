@@ -53,7 +53,7 @@ constexpr int64_t kTopKChunk = 256;       // tokens per chunk of the unfused top
 constexpr int kTopKChunks = 1024, kTopKChunkUnit = 64, kTopKWave = 1024;
 constexpr int kTopKFusedK = 6;            // largest k of the fused single-token top-k
 constexpr int kTopKMergeBlock = 1024;     // threads of the round-based top-k merge workgroup
-constexpr int kTopKMergeC = 8;            // candidates per thread of that merge (else the scan merge)
+constexpr int kTopKMergeC = 8;            // candidates per thread of that merge
 
 archead_status fail(archead_status s, const char* fmt, ...);
 void clear_error();
@@ -119,7 +119,7 @@ struct WsLayout {
   int64_t tk_chunk = 0;   // tokens per chunk (unfused)
   size_t tk_lg_off = 0;   // fp32 [chunk][V]
   size_t tk_in_off = 0;   // workspace of the chunk's logits call
-  size_t tk_pv_off = 0;   // fused: fp32 [n_part][kTopKMax] partial lists
+  size_t tk_pv_off = 0;   // fused: fp32 [n_part][kTopKFusedK] partial lists
   size_t tk_pi_off = 0;   // int32, the same shape
   size_t tk_key_off = 0;  // unfused: uint32 [chunk][tk_n_chunk] order keys of the rows' chunk maxima
   int tk_cs = 0, tk_n_chunk = 0;   // logits per chunk of a row, chunks

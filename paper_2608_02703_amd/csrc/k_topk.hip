@@ -37,33 +37,6 @@ const void* gemv_topk_fn(int lpr, bool sc8) {
   return reinterpret_cast<const void*>(fn);
 }
 
-// Offer entries j in [lo, hi) of one wave's share of a flat array of
-// candidates (value val(j), index idx(j)) to the wave's list: 64 per step,
-// wave w of the workgroup taking steps lo + 64 w, lo + 64 (w + kWaves), ...;
-// kScanBatch steps' loads are issued together before any is offered, so a
-// scan costs one memory latency per batch, not per step.  Candidates ranked
-// below the floor (fv, fi) are not offered.
-constexpr int kScanBatch = 8;
-template <typename Val, typename Idx>
-__device__ __forceinline__ void tk_scan(int64_t lo, int64_t hi, Val val, Idx idx, int lane, int wid,
-                                        int k, float& lv, int& li, float& bv, int& bi,
-                                        float fv = -INFINITY, int fi = kNoIdx) {
-  for (int64_t b = lo + int64_t(wid) * 64; b < hi; b += int64_t(kScanBatch) * kBlock) {
-    float cv[kScanBatch];
-    int ci[kScanBatch];
-#pragma unroll
-    for (int u = 0; u < kScanBatch; ++u) {
-      const int64_t j = b + int64_t(u) * kBlock + lane;
-      cv[u] = j < hi ? val(j) : -INFINITY;
-      ci[u] = j < hi ? idx(j) : kNoIdx;
-    }
-#pragma unroll
-    for (int u = 0; u < kScanBatch; ++u)
-      tk_offer(lv, li, bv, bi, cv[u], ci[u],
-               (b + int64_t(u) * kBlock + lane < hi) & !tk_better(fv, fi, cv[u], ci[u]), lane, k);
-  }
-}
-
 __device__ __forceinline__ void tk_pick(float& bv, int& bi, float ov, int oi) {
   const bool t = tk_better(ov, oi, bv, bi);
   bv = t ? ov : bv;
@@ -350,55 +323,11 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
   }
 }
 
-// Per token m (grid M, workgroups of kBlock): the k best of its n_part partial
-// lists of k pairs (scanned as one flat array of n_part * k candidates), out to
-// vals[m * ldk + j] (may be null) and idx[m * ldk + j], j < k; a slot no
-// value reached (fewer than k non-NaN logits) gets (-inf, -1).
-__global__ __launch_bounds__(kBlock) void k_topk_merge_scan(const float* pv, const int* pi,
-                                                       int64_t n_part, int k, float* vals,
-                                                       int64_t* idx, int64_t ldk) {
-  __shared__ float sv[kWaves * 64];
-  __shared__ int si[kWaves * 64];
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-  const int64_t m = blockIdx.x;
-  const float* v = pv + m * n_part * k;
-  const int* ix = pi + m * n_part * k;
-  // a floor for the result's k-th entry: each list holds k entries ranked at
-  // or above its own k-th, so the best of the lists' k-th entries is ranked
-  // at or below the final k-th; candidates ranked below it are skipped
-  float fv = -INFINITY;
-  int fi = kNoIdx;
-  for (int64_t p = threadIdx.x; p < n_part; p += kBlock) {
-    const float c = v[p * k + k - 1];
-    const int ci = ix[p * k + k - 1];
-    if (tk_better(c, ci, fv, fi)) { fv = c; fi = ci; }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float ov = __shfl_xor(fv, off, 64);
-    const int oi = __shfl_xor(fi, off, 64);
-    if (tk_better(ov, oi, fv, fi)) { fv = ov; fi = oi; }
-  }
-  if (lane == 0) { sv[wid] = fv; si[wid] = fi; }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w)
-    if (tk_better(sv[w], si[w], fv, fi)) { fv = sv[w]; fi = si[w]; }
-  __syncthreads();
-  float lv = -INFINITY, bv = -INFINITY;
-  int li = kNoIdx, bi = kNoIdx;
-  tk_scan(0, n_part * k, [&](int64_t j) { return v[j]; }, [&](int64_t j) { return ix[j]; }, lane,
-          wid, k, lv, li, bv, bi, fv, fi);
-  tk_block_merge<kWaves>(lv, li, bv, bi, lane, wid, k, sv, si);
-  if (wid == 0 && lane < k) {
-    if (vals) vals[m * ldk + lane] = lv;
-    idx[m * ldk + lane] = li == kNoIdx ? int64_t(-1) : int64_t(li);
-  }
-}
-
-// Per token m (grid M, workgroups of kMergeBlock), for at most kMergeBlock *
-// kMergeC candidates: the same result in k rounds.  Each thread holds up to
+// Per token m (grid M, workgroups of kMergeBlock): the k best of its n_part
+// partial lists of k pairs, at most kMergeBlock * kMergeC candidates in all, out
+// to vals[m * ldk + j] (may be null) and idx[m * ldk + j], j < k; a slot no
+// value reached (fewer than k non-NaN logits) gets (-inf, -1).  It takes k
+// rounds.  Each thread holds up to
 // kMergeC candidates and its best one; a round finds the best of the
 // workgroup (DPP within rows of 16 lanes, then the four rows of the wave,
 // then the waves through LDS), writes it out, and its owner (indices are
@@ -492,7 +421,6 @@ const void* topk_merge(int block) {
   return block == 256 ? reinterpret_cast<const void*>(k_topk_merge<256>)
                       : reinterpret_cast<const void*>(k_topk_merge<1024>);
 }
-const void* topk_merge_scan() { return reinterpret_cast<const void*>(k_topk_merge_scan); }
 
 }  // namespace kern
 }  // namespace archead

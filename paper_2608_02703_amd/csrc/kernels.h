@@ -18,7 +18,6 @@ const void* gemv_topk(int lpr, bool sc8, int gen);
 const void* topk_max(int cs);      // the maxima of the rows' chunks, then
 const void* topk_select();   // the k best from the chunks that can hold one
 const void* topk_merge(int block);   // k rounds; workgroups of 256 or kTopKMergeBlock threads, kTopKMergeC candidates each
-const void* topk_merge_scan();   // any number of candidates
 // MFMA decode kernel k_dec<GW, CE, EK, SC8, GEN>: gw = g / 32 code words per
 // lane and group (1, 2, 4), ek expansion K-chunks held (2 or 4), gen as for
 // gemv (every variant exists)

@@ -11,7 +11,8 @@ entries' fp64 logits must lie within that tolerance of each other.
 
 Cases: every kernel (forced) and the library's choice, M = 1 (the fused
 single-token GEMV), small M on the decode kernels, several token tiles, and
-M = 300 (two chunks of the unfused path, the second ragged); k = 1, 10, 64;
+M = 300 (two chunks of the unfused path, the second ragged); k = 1, 10, 64,
+and for one token (whose lists the GEMV keeps up to k = 6) also 2, 5, 6;
 8-bit scale codes, 5-bit core-left codes with ranks 10 / 6, a ragged V;
 vocabulary rows duplicated so that exact ties land in the top k; and the
 Qwen3-8B-shaped head at M = 1 against the full fp64 oracle logits.
@@ -95,7 +96,7 @@ def test_topk_every_kernel(label, kw):
                          ("mid", (21,)), ("tiled", (1, 70))):
             ph.force_path(path)
             for M in Ms:
-                for k in (1, 10, 64):
+                for k in (1, 2, 5, 6, 10, 64) if M == 1 else (1, 10, 64):
                     say(f"top-k {label}: {path} M={M} k={k}")
                     ref = ref_all[:M] if M <= 40 else None
                     _check(ph, x_all[:M], k, ref, f"{label} {path} M={M}")
@@ -117,13 +118,14 @@ def test_topk_exact_ties():
             ph.force_path(path)
             say(f"top-k ties: {path} M={M}")
             xt = torch_x(x[:M])
-            vals, idx = ph.logits_topk(xt, 10)
-            torch.cuda.synchronize()
-            idx = idx.cpu().numpy()
-            # token 0: the tied copies lead, in index order
             want = np.array(sorted(list(dst) + [top]))
-            assert np.array_equal(idx[0, :want.size], want), (path, idx[0], want)
-            _check(ph, x[:M], 10, what=f"ties {path}")
+            for k in (3, 6, 10) if M == 1 else (10,):
+                vals, idx = ph.logits_topk(xt, k)
+                torch.cuda.synchronize()
+                idx = idx.cpu().numpy()
+                # token 0: the tied copies lead, in index order
+                assert np.array_equal(idx[0, :min(k, want.size)], want[:k]), (path, k, idx[0], want)
+                _check(ph, x[:M], k, what=f"ties {path}")
     finally:
         ph.close()
 
@@ -137,7 +139,7 @@ def test_topk_qwen_single_token_fused():
         x = make_x("qwen_decode", 1)
         say("top-k qwen M=1 (fused GEMV): oracle logits")
         ref = ohead.logits(h, x)
-        for k in (1, 10, 64):
+        for k in (1, 2, 3, 5, 6, 10, 64):   # (768 lists: the sixteen-wave merge from k = 3 on)
             say(f"top-k qwen M=1 k={k}")
             _check(ph, x, k, ref, "qwen M=1")
     finally:
@@ -164,11 +166,12 @@ def test_topk_argument_checks():
         ph.close()
 
 
-@pytest.mark.parametrize("V", [70, 255, 1025, 5000, 65536, 65537, 270000])
+@pytest.mark.parametrize("V", [70, 255, 1025, 5000, 65536, 65537, 270000, 1050000])
 def test_topk_chunk_edges(V):
     """Rows of less than k chunks, of exactly some chunks and one more, and
-    around the lengths where the chunk grows (64, 256, 512 logits); logits equal in many chunks (more ties than the candidate buffer
-    holds), signed zeros, infinities, NaN, and fewer than k numbers in a row."""
+    around the lengths where the chunk grows (64, 256, 1024, 2048 logits); logits
+    equal in many chunks (more ties than the candidate buffer holds), signed
+    zeros, infinities, NaN, and fewer than k numbers in a row."""
     from paper_2608_02703_amd import PackedHead
     # one group, no factors: logit[m, v] = scale[v] * (code row 0) . x[m]
     h = make_head("tiny", V=V, d=64, g=64, rc=0, rr=0)
@@ -210,6 +213,28 @@ def test_topk_chunk_edges(V):
                         assert np.array_equal(vals[m].view(np.uint32), wv.view(np.uint32))
         finally:
             ph.close()
+
+
+def test_topk_fused_grids():
+    """The fused form's lists under other grids: few lists (the four-wave
+    merge), many (the sixteen-wave one), and more than that holds, where one
+    token takes the unfused form."""
+    from paper_2608_02703_amd import PackedHead, archead as ab
+    h = make_head("tiny", V=60000, d=2048, rc=256, rr=32)   # (32 rows a workgroup: up to 1875)
+    x = make_x("tiny", 1, d=h.d)
+    ph = PackedHead.from_arrays(h)
+    ph.force_path("gemv")
+    try:
+        need = {}
+        for grid in (7, 300, 700, 1365, 1366, 1800):
+            ph.set_launch(ab.LAUNCH_GEMV_GRID, grid)
+            need[grid] = ph.workspace_bytes(1, ab.OP_TOPK)
+            for k in (1, 3, 6, 7):
+                say(f"top-k GEMV grid {grid} k={k}")
+                _check(ph, x, k, what=f"grid {grid}")
+        assert need[1366] < need[1365]      # (no lists beside the logits)
+    finally:
+        ph.close()
 
 
 @pytest.mark.parametrize("M,d", [(2100, 2048), (4100, 1024)])
