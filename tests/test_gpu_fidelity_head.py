@@ -12,7 +12,8 @@ head's fp32 logits, so it is checked exactly against those logits
 (archead_logits, the same per-element arithmetic) and the GPU's own top-1.
 Dense heads near the packed one (small KL, top-1 mostly kept) and unrelated
 to it (large KL); ragged vocabulary and token tiles; 8-bit scales and 5-bit
-U_c; a dense head with a row stride wider than d; the Qwen3-8B shape.
+U_c; an odd number of residual stages before an even and an odd number of
+expansion stages and before none; a dense head with a row stride wider than d; the Qwen3-8B shape.
 """
 from __future__ import annotations
 
@@ -87,6 +88,9 @@ def _check(ph, h, w_bits, x, what, ld=None):
     ("u8 scales", dict(scales="u8"), 0.05),
     ("i5 rc10 rr6 g64", dict(rc=10, rr=6, core_u="i5", scales="u8"), 0.02),
     ("ragged V", dict(V=1000), 0.02),
+    ("d 192", dict(V=1000, d=192, g=64, rc=0, rr=0), 0.02),
+    ("d 320", dict(V=1000, d=320, g=64, rc=16, rr=4), 0.02),
+    ("d 448", dict(V=1000, d=448, g=448, rc=20, rr=12), 0.02),
 ])
 def test_fidelity_head_matches_oracle(label, kw, eps):
     from paper_2608_02703_amd import PackedHead

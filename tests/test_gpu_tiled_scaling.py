@@ -5,8 +5,9 @@ the logits are scaled back, so a row's magnitude must not matter: rows of
 magnitudes 2^-100 .. 2^90, a zero row and a subnormal row against the oracle,
 a row with an infinity and one with a NaN (all logits of those rows are NaN,
 their neighbours are untouched), on heads with ragged vocabulary, groups of
-64, 128 and 192 (one to three stages per scale slot), both, one or no
-expansion part, zero scales and 8-bit scales; logits into rows that take the
+64, 128 and 192 (one to three stages per scale slot), with an odd number of
+residual stages (the codes come for two) followed by an even and an odd number
+of expansion stages and by none, both, one or no expansion part, zero scales and 8-bit scales; logits into rows that take the
 16-byte stores and rows that do not, fp32 and bf16.
 """
 from __future__ import annotations
@@ -42,9 +43,15 @@ def _gpu():
     (dict(V=1000, d=512, g=128, rc=40, rr=0, scales="u8"), 130),
     (dict(V=256, d=512, g=64, rc=0, rr=0), 300),
     (dict(V=77, d=64, g=64, rc=16, rr=4), 33),      # a single stage per part
+    # an odd number of residual stages, in every tile layout below
+    (dict(V=300, d=192, g=64, rc=0, rr=0), 300),
+    (dict(V=300, d=192, g=192, rc=16, rr=0), 64),
+    (dict(V=300, d=320, g=64, rc=16, rr=4), 130),
+    (dict(V=300, d=320, g=320, rc=0, rr=20, scales="u8"), 65),
+    (dict(V=300, d=448, g=64, rc=20, rr=16), 1100),
 ])
 def test_row_magnitudes(kw, M):
-    from paper_2608_02703_amd import PackedHead
+    from paper_2608_02703_amd import PackedHead, archead as ab
     h = make_head("tiny", **kw)
     h.res_scales[::7, 0] = 0            # zero scales inside a row
     h.res_scales[5] = 0                 # and a row of nothing else
@@ -61,9 +68,12 @@ def test_row_magnitudes(kw, M):
     ph = PackedHead.from_arrays(h)
     ph.force_path("tiled")
     try:
-        for pad in (0, 1, 4):
+        layouts = [(0, 0)] + [(4, 64), (4, 128), (8, 0)] * (kw["d"] // 64 % 2)
+        for waves, rows, pad in [(*la, pad) for la in layouts for pad in (0, 1, 4)]:
+            ph.set_launch(ab.LAUNCH_TILE_WAVES, waves)
+            ph.set_launch(ab.LAUNCH_TILE_ROWS, rows)
             for dtype in (torch.float32, torch.bfloat16):
-                say(f"tiled scaling {kw} M={M} pad={pad} {dtype}")
+                say(f"tiled scaling {kw} M={M} pad={pad} {dtype} layout {waves} {rows}")
                 out = torch.full((M, V + pad + 3), 3.0, device="cuda", dtype=dtype)
                 ph.logits(torch_x(x), out=out[:, :V], out_dtype=dtype)
                 torch.cuda.synchronize()
