@@ -154,18 +154,20 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
     const int enough = k + k / 4 + 3;   // (reading a few chunks more is cheaper than 12 steps more)
     uint32_t f = 0;
     int reach = n_chunk;   // maxima that reach f
-    for (int bit = n_chunk < k ? -1 : 31; bit >= 12 || (bit >= 0 && reach > enough); --bit) {
+    auto step = [&](int bit) {
       const uint32_t t = f | (1u << bit);
       int n = 0;
 #pragma unroll
       for (int i = 0; i < kSelWaves; ++i) n += __popcll(__ballot(kk[i] >= t));
-      if (n >= k) {
-        f = t;
-        reach = n;
-      }
-    }
+      f = n >= k ? t : f;
+      reach = n >= k ? n : reach;
+    };
+#pragma unroll
+    for (int bit = 31; bit >= 12; --bit) step(bit);
+#pragma unroll 1
+    for (int bit = 11; bit >= 0 && reach > enough; --bit) step(bit);
     int most = kSelBlock;
-    if (f && reach > enough) {
+    if (__builtin_expect(f && reach > enough, 0)) {
       // Many maxima equal to f: the first k - (maxima above f) of their chunks
       // hold as many of the logits equal to f as can be wanted, those of the
       // smallest indices among them; no other chunk of f's is read.
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
   const uint32_t fl = sfloor;
   const uint64_t lower = (uint64_t(1) << lane) - 1;
   bool listed = mine >= fl;
-  if (smost < kSelBlock) {
+  if (__builtin_expect(smost < kSelBlock, 0)) {
     const uint64_t tie = __ballot(mine == fl);
     listed = mine > fl || (mine == fl && sties[wid] + __popcll(tie & lower) < smost);
   }
@@ -223,7 +225,7 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
   }
   __syncthreads();
   int nc = ncand;
-  if (nc > kSelCand) {
+  if (__builtin_expect(nc > kSelCand, 0)) {
     // More than are ranked one against all: the k best of them, some units
     // a wave at a time together with the k best so far, by a search for the
     // k-th largest key and among its equals for the largest index taken; the
