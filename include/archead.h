@@ -227,9 +227,11 @@ size_t archead_workspace_bytes(const archead_handle* h, int64_t M, archead_op op
  * workspace; the others wait for it a bounded time and otherwise compute it
  * themselves), so a decode step is a single kernel launch;
  *   - otherwise the tiled bf16 MFMA kernel (tiles of 64 tokens x 256
- *     vocabulary rows, three workgroups per CU, up to M = 64; 128 x 256,
- *     two workgroups per CU, up to M = 1024; 256 x 256 tiles above; its head-derived tables are built per call unless
- *     archead_prepare keeps them).
+ *     vocabulary rows, three workgroups per CU, up to M = 64; those or tiles
+ *     of 128 x 256, two workgroups per CU, up to M = 1024, whichever fill
+ *     their rounds of workgroups better; 256 x 256 tiles above; its
+ *     head-derived tables are built per call unless archead_prepare keeps
+ *     them).
  * All produce fp32 logits from fp32 accumulation.  The tiled kernel carries
  * its accumulator in units of the current scale group's scale and feeds the
  * rank-r expansion t as three bf16 parts (t to fp32 precision), so its

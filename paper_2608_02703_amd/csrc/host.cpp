@@ -129,8 +129,11 @@ void default_ranges(const archead_desc& d, int64_t (&r)[4]) {
     r[0] = dec_min_m(d);
     r[1] = tpp;
     r[2] = tpp + 1;
-    // at d >= 8192 the tiled kernel overtakes it from 24 tokens on (128k
-    // head: 198 / 224 us at M = 24 / 32 against 201 / 202 tiled)
+    // at d >= 8192 the tiled kernel is ahead from 17 tokens on with its tables
+    // prepared and not up to 32 without (128k head, us at M = 17 / 24 / 32: 190
+    // / 202 / 228, tiled 183 / 187 / 189 and 264 / 265 / 266); 24 lies between.
+    // On narrower heads it is ahead of both up to 32 (at 32, Qwen and Gemma
+    // shapes: 118 and 140 against 126 / 164 and 149 / 203)
     r[3] = d.d >= 8192 ? 24 : kDefaultMidMaxM;
   } else {
     r[0] = dec_min_m(d);
