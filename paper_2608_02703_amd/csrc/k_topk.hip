@@ -68,8 +68,8 @@ __device__ __forceinline__ void tk_row16_best(float& v, int& i) {
 // the caches for the usual sizes; the second is a chain of short steps of one
 // workgroup per token.  24 tokens of 128256 logits, k = 50: 5.5 + 9.3 us
 // (sorted lists per slice and a merge in k rounds: 61 + 52 us).  24 tokens of
-// 151936 logits, k = 10 / 50, both: random 17 / 20 us, around 1000 18 / 21, all
-// equal 28 / 44, ascending 28 / 49.
+// 151936 logits, k = 10 / 50, both: random 16 / 19 us, around 1000 18 / 21, all
+// equal 26 / 39, ascending 22 / 33.
 //
 // Order key of a logit: larger for larger values, equal for equal ones (0 and
 // -0), 0 for NaN (which is never selected).
@@ -233,11 +233,24 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
     uint32_t top = mine;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) top = max(top, uint32_t(__shfl_xor(int(top), off, 64)));
-    if (lane == 0) skey[wid] = top;   // (its words were read above)
+    const uint64_t lm = __ballot(listed);
+    if (lane == 0) {   // (skey's words were read above)
+      skey[wid] = top;
+      skey[kSelWaves + wid] = lm ? 64 * wid + __builtin_ctzll(lm) : kSelBlock;
+      skey[2 * kSelWaves + wid] = lm ? 64 * wid + 63 - __builtin_clzll(lm) : 0;
+    }
     __syncthreads();
+    uint32_t c_lo = kSelBlock, c_hi = 0;   // first and last chunk listed
 #pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) top = max(top, skey[w]);
+    for (int w = 0; w < kSelWaves; ++w) {
+      top = max(top, skey[w]);
+      c_lo = min(c_lo, skey[kSelWaves + w]);
+      c_hi = max(c_hi, skey[2 * kSelWaves + w]);
+    }
     const int high = top == fl ? -1 : 31 - __builtin_clz(top ^ fl);   // the keys agree above it
+    // and the indices above this one (cs > 1: they differ somewhere)
+    const uint32_t j_lo = c_lo * uint32_t(cs), j_hi = c_hi * uint32_t(cs) + uint32_t(cs - 1);
+    const int j_high = 31 - __builtin_clz(j_lo ^ j_hi);
     int have = 0, end = int(V);
     uint32_t f = fl;
     auto reduce = [&](auto units_per_wave) {
@@ -284,8 +297,8 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
           if (reach != k) {
             const int want = k - count(&scount[0][33], [&](uint32_t kb, int) { return kb > f; });
             int n = -1;
-            end = 0;
-            for (int bit = 31 - __builtin_clz(int(V)); bit >= 0 && n != want; --bit) {
+            end = int(j_lo >> j_high >> 1 << 1 << j_high);
+            for (int bit = j_high; bit >= 0 && n != want; --bit) {
               const int t = end | (1 << bit);
               n = count(&scount[1][bit], [&](uint32_t kb, int jb) { return kb == f && jb < t; });
               if (n <= want) end = t;
