@@ -361,13 +361,14 @@ archead_status archead_logits_topk(const archead_handle* h, const void* x, int64
  *     2 s and d/g / (2 s) >= 8 (r_c + r_r = 0: s = 1).
  *   The static memory holds every accepted call of groups up to 128 in one
  *   pass; of larger groups, calls whose copy of x (2 * M * d bytes) does not
- *   fit run in several chunks of tokens.
+ *   fit run in several chunks of tokens, as do those that need the larger
+ *   array where archead_create found no memory for it.
  *   All calls on one GPU share that GPU's memory, which keeps the last call's
  *   contents (no call needs it cleared): calls that overlap on one GPU, on
  *   different streams or from different threads, race and give undefined
  *   results; serialise them.
- * Errors as archead_logits.  ARCHEAD_E_HIP from archead_create when an
- * address could not be taken. */
+ * Errors as archead_logits.  ARCHEAD_E_HIP from archead_create when the
+ * small array's address could not be taken. */
 archead_status archead_logits_noalloc(const archead_handle* h, const void* x, int64_t M,
                                       int64_t ldx, void* out, archead_dtype out_dtype,
                                       int64_t ldo, void* stream);

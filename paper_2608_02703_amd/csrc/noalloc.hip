@@ -55,10 +55,11 @@ archead_status scratch_setup(const archead_handle* h) {
     g_scratch[device] = p;
   }
   if (!g_large[device] && noalloc_wants(h, kScratchBytes)) {
+    // (no memory for it is no reason to refuse the head: its calls then run in
+    // chunks that the small array holds)
     void* p = nullptr;
-    const archead_status st = scratch_large(&p);
-    if (st != ARCHEAD_OK) return st;
-    g_large[device] = p;
+    if (scratch_large(&p) == ARCHEAD_OK) g_large[device] = p;
+    else (void)hipGetLastError();
   }
   return ARCHEAD_OK;
 }

@@ -13,9 +13,7 @@ namespace archead {
 archead_status scratch_large(void** p) {
   *p = nullptr;
   const hipError_t e = hipGetSymbolAddress(p, HIP_SYMBOL(scratch_l));
-  if (e != hipSuccess || !*p)
-    return fail(ARCHEAD_E_HIP, "hipGetSymbolAddress(scratch_l): %s", hipGetErrorString(e));
-  return ARCHEAD_OK;
+  return e == hipSuccess && *p ? ARCHEAD_OK : ARCHEAD_E_HIP;
 }
 
 }  // namespace archead
