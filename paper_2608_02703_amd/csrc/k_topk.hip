@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kSelBlock) void k_topk_select(const float* logits, 
     auto reduce = [&](auto units_per_wave) {
       constexpr int kRedUnits = decltype(units_per_wave)::value;
       for (int r0 = 0; r0 < units; r0 += kRedUnits * kSelWaves) {
-        // element 0: one of the k best so far; then this round's that may join them
+        // element 0: one of the k best so far; then those read now that may join them
         uint32_t key[kRedUnits + 1];
         int j[kRedUnits + 1];
         j[0] = tid < have ? cidx[tid] : int(V);
