@@ -853,6 +853,7 @@ constexpr int kS1MTok = 16, kS1MCols = 64, kS1MBlock = 512, kS1MWaves = kS1MBloc
 // Workgroups of the two launches along x; more go on along y (2^22 of
 // kS1MBlock threads stay below the 2^32 of a launch's dimension).
 constexpr int64_t kGridX = int64_t(1) << 22;
-__device__ __forceinline__ int64_t stage1_block() { return int64_t(blockIdx.y) * gridDim.x + blockIdx.x; }
+// (a launch with rows along y has kGridX along x: no read of the grid's size)
+__device__ __forceinline__ int64_t stage1_block() { return int64_t(blockIdx.y) * kGridX + blockIdx.x; }
 
 }  // namespace
